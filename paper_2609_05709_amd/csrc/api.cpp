@@ -98,7 +98,9 @@ struct soap_ctx {
     NbrWork nw{};
     DevBuf b_zero, b_bstart, b_acell, b_srec, b_sspec, b_deg, b_slots, b_scan, b_spec, b_row, b_cols, b_cscratch;
     DevBuf b_avg, b_avg_part; // averaged modes: per-center rows, column partial sums and means
-    DevBuf b_radial;          // polynomial quadrature: radial factors of a call's edges
+    DevBuf b_rtab;            // table of the radial factors
+    int rtab_kind = 0;        // what it holds: 0 nothing, 4 / 8 float32 / float64 records
+    DevBuf b_radial;          // radial factors of a call's edges, where they don't go to its edge blocks
     std::vector<int64_t> h_row; // polynomial quadrature: host copy of the CSR row offsets
     // periodic cell (soap_set_cell) and the extended structure of the last build
     bool periodic = false, built_periodic = false;
@@ -116,6 +118,7 @@ struct soap_ctx {
     // state of the last neighbour build
     bool have_rows = false;
     int64_t n_atoms = 0, nc = 0, E = 0;
+    int maxdeg = 0; // largest number of neighbours of a center
     const void *pos = nullptr;
     const int32_t *Zdev = nullptr, *centers = nullptr;
     bool built_f64 = false;
@@ -126,6 +129,8 @@ struct soap_ctx {
     // one path still serves the others (the descriptor path is required)
     bool dens_ok[3] = {false, false, false}, out_ok = false, jac_ok = false;
     JacLaunch jac_cfg{};
+    bool inline_radial = false; // the Jacobian path evaluates the radial factors in its kernels (no radial pass)
+    EdgeBlocksLaunch eb_cfg{}; // the edge Jacobian kernel (threads 0: k_jacobian)
     DescLaunch desc_cfg{};
     DjacLaunch djac_cfg{};
     int djac_tile = 0; // option "djac_tile": 0 auto (default), -1 never k_djac, else the widest chunk
@@ -256,6 +261,8 @@ int kernel_basis(const soap_ctx *c) {
     return c->rbf;
 }
 
+bool reads_radial(const soap_ctx *c, int mode);
+
 int plan_launches(soap_ctx *c) {
     Params &P = c->P;
     P.rbf = kernel_basis(c);
@@ -266,14 +273,17 @@ int plan_launches(soap_ctx *c) {
     const bool f64d = c->dtype == SOAP_FP64;
     c->ar64 = !f64d && c->arith == SOAP_ARITH_FP64;
     const bool ar64 = c->ar64, st64 = f64d || ar64;
+    Params Pb = P; // the Jacobian path reads the radial pass's factors
+    Pb.rbf = RBF_BUFFERED;
     for (int mode = 0; mode < 3; ++mode) {
         const int jac = mode != 0; // modes 1 and 2 stage gradients
         int *lgrp = c->lgrp[mode], *G = &c->groups[mode];
+        const Params &Pm = mode == 1 ? Pb : P;
         // workgroups per CU the registers allow (no LDS), and the LDS share of each
         auto plan = [&](bool hi, int *lg, int *g, int *w, size_t *ld) {
-            const int by_regs = std::max(1, density_blocks_per_cu(f64d, ar64, mode, P.rbf, hi, 0));
+            const int by_regs = std::max(1, density_blocks_per_cu(f64d, ar64, mode, Pm.rbf, hi, 0));
             const size_t budget = std::min(LDS_HARD_LIMIT, (size_t)(159 * 1024) / (size_t)by_regs);
-            return plan_groups(P, jac, st64, budget, lg, g, w, ld) == 0;
+            return plan_groups(Pm, jac, st64, budget, lg, g, w, ld) == 0;
         };
         c->dens_ok[mode] = plan(false, lgrp, G, &Wd, &lds);
         if (!c->dens_ok[mode]) {
@@ -281,19 +291,17 @@ int plan_launches(soap_ctx *c) {
             continue;
         }
         bool hi = false;
-        if (density_has_high(mode, P.rbf)) {
+        if (mode == 2) {
             // more workgroups per CU hide more latency, but split the LDS
-            // further.  The Jacobian path takes three waves per SIMD only if
-            // the plan keeps its l-groups and at least two edges per tile
-            // (measured: 3% faster at n_max 8, l_max 6; up to twice as slow
-            // where the tiles shrink).  "cc" takes two waves whenever they
-            // plan (faster in 3 of 4 measured bases, by 13-29%; 13% slower at
+            // further.  "cc" takes two waves per SIMD whenever they plan
+            // (faster in 3 of 4 measured bases, by 13-29%; 13% slower at
             // n_max 12, l_max 12, where no simple rule on the plan told apart)
             int lg3[MAX_GROUPS + 1], G3 = 0, W3 = 0;
             size_t lds3 = 0;
-            if (plan(true, lg3, &G3, &W3, &lds3) && (mode == 2 || (G3 == *G && W3 >= 2))) {
+            if (plan(true, lg3, &G3, &W3, &lds3)) {
                 hi = true;
                 std::copy(lg3, lg3 + G3 + 1, lgrp);
+                *G = G3;
                 Wd = W3;
                 lds = lds3;
             }
@@ -301,7 +309,7 @@ int plan_launches(soap_ctx *c) {
         c->dens_cfg[mode].W = Wd;
         c->dens_cfg[mode].lds = lds;
         c->dens_cfg[mode].hi = hi;
-        const int per_cu = density_blocks_per_cu(f64d, ar64, mode, P.rbf, hi, lds);
+        const int per_cu = density_blocks_per_cu(f64d, ar64, mode, Pm.rbf, hi, lds);
         c->dens_cfg[mode].blocks = std::max(1, ncu * per_cu / *G);
     }
     c->out_ok = plan_outputs(P, c->dtype == SOAP_FP64, st64, c->out_rows, &c->out_plan) == 0;
@@ -313,18 +321,39 @@ int plan_launches(soap_ctx *c) {
     // 0.76 against 1.05 ms per Jacobian launch; one workgroup of two-edge
     // tiles loses to two of one-edge tiles, CHNO 0.91 against 0.81 ms)
     const bool f64 = c->dtype == SOAP_FP64;
-    int bestW = 0, bestB = 0;
-    for (int W = jacobian_max_w(); W >= 1; --W) {
-        if (c->jac_tile > 0 && W != c->jac_tile) continue;
-        const size_t lds = jacobian_lds_bytes(P, W, st64);
-        if (lds > LDS_HARD_LIMIT) continue;
-        int b = jacobian_blocks_per_cu(f64, ar64, P.rbf, P.n, P.lmax + 1, lds);
-        if (W >= 2 && b >= 2) b *= 2;
-        if (b > bestB) {
-            bestB = b;
-            bestW = W;
+    int bestW = 0;
+    auto plan_jacobian = [&](const Params &Pj) { // -> workgroups per CU (a wide tile's count double, as above)
+        int best = 0;
+        bestW = 0;
+        for (int W = jacobian_max_w(); W >= 1; --W) {
+            if (c->jac_tile > 0 && W != c->jac_tile) continue;
+            const size_t lds = jacobian_lds_bytes(Pj, W, st64);
+            if (lds > LDS_HARD_LIMIT) continue;
+            int b = jacobian_blocks_per_cu(f64, ar64, Pj.rbf, P.n, P.lmax + 1, lds);
+            if (W >= 2 && b >= 2) b *= 2;
+            if (b > best) {
+                best = b;
+                bestW = W;
+            }
         }
+        c->jac_cfg.W = bestW;
+        c->jac_cfg.lds = bestW > 0 ? jacobian_lds_bytes(Pj, bestW, st64) : 0;
+        return best;
+    };
+    // The radial factors: evaluated inside k_djac and k_jacobian (GTO), or by
+    // the radial pass for the kernels of the other paths.  k_jacobian with its
+    // own factors is the faster one where it keeps its workgroups resident
+    // with tiles of two edges or more: three of them per CU in float32, two in
+    // float64 (3000-atom water: n_max 8, l_max 6 0.41 against 0.44 ms for k_edge_blocks, float64 0.80
+    // against 0.83; at n_max 12, l_max 12, where it runs one workgroup, 2.86
+    // against 1.77)
+    c->inline_radial = false;
+    if (P.rbf == 0 && c->djac_tile >= 0) {
+        const int b = plan_jacobian(P);
+        c->inline_radial = c->jac_tile > 0 ? b > 0 // asks for k_jacobian
+                                           : !ar64 && b >= (f64 ? 4 : 6);
     }
+    if (!c->inline_radial) plan_jacobian(Pb);
     // descriptor kernel: the widest chunk of edges that keeps at least two
     // workgroups (of four waves) resident per CU; an explicit "desc_tile" is
     // the widest chunk tried, and any chunk that fits at all is taken
@@ -343,43 +372,68 @@ int plan_launches(soap_ctx *c) {
             }
         }
     }
-    // density step of the Jacobian path (GTO): the widest chunk of edges that
-    // keeps at least two workgroups resident per CU
-    c->djac_cfg = DjacLaunch{};
-    int qt = 0, na2 = 0, sr = 0;
-    if (c->djac_tile >= 0 && djac_shape(P, &qt, &na2, &sr)) {
+    // density step of the Jacobian path: the widest chunk of edges that keeps
+    // at least two workgroups resident per CU.  For the polynomial bases an
+    // explicit "djs_tile" chooses among the other two kernels.
+    auto plan_djac = [&](const Params &Pd) {
+        c->djac_cfg = DjacLaunch{};
+        int qt = 0, na = 0, sr = 0;
+        if (c->djac_tile < 0 || (c->rbf != SOAP_RBF_GTO && c->djs_tile != 0) || !djac_shape(Pd, &qt, &na, &sr)) return;
         for (int W : {64, 32}) {
             if (c->djac_tile > 0 && W > c->djac_tile) continue;
-            const size_t lds = djac_lds_bytes(P, W, st64);
+            const size_t lds = djac_lds_bytes(Pd, W, st64);
             if (lds > LDS_HARD_LIMIT) continue;
-            const int b = djac_blocks_per_cu(f64, ar64, qt, na2, sr, lds);
+            const int b = djac_blocks_per_cu(f64, ar64, Pd.rbf, qt, na, sr, lds);
             if (b >= (c->djac_tile > 0 ? 1 : 2)) {
-                c->djac_cfg = DjacLaunch{W, qt, na2, sr, lds, ncu * b};
+                c->djac_cfg = DjacLaunch{W, qt, na, sr, lds, ncu * b};
                 break;
             }
         }
+    };
+    if (c->inline_radial) {
+        plan_djac(P);
+        if (c->djac_cfg.W == 0) { // the other density kernels read the radial pass's factors
+            c->inline_radial = false;
+            plan_jacobian(Pb);
+        }
     }
-    // density step of the Jacobian path for the other GTO and polynomial
-    // quadrature bases: coefficients streamed to the scratch, outputs by the
+    if (!c->inline_radial) plan_djac(Pb);
+    // the other bases: coefficients streamed to the scratch, outputs by the
     // output kernel.  The widest chunk of edges that keeps at least two
     // workgroups resident per CU.
     c->djs_cfg = DjsLaunch{};
-    int qs = 0, nas = 0;
-    if (c->djac_cfg.W == 0 && c->djs_tile >= 0 && c->out_ok && djs_shape(P, &qs, &nas)) {
+    int qs = 0;
+    if (c->djac_cfg.W == 0 && c->djs_tile >= 0 && c->out_ok && djs_shape(Pb, &qs)) {
         for (int W : {64, 32, 16}) {
             if (c->djs_tile > 0 && W > c->djs_tile) continue;
-            const size_t lds = djs_lds_bytes(P, W, st64);
+            const size_t lds = djs_lds_bytes(Pb, W, st64);
             if (lds > LDS_HARD_LIMIT) continue;
-            const int b = djs_blocks_per_cu(f64d, ar64, P.rbf, qs, nas, lds);
+            const int b = djs_blocks_per_cu(f64d, ar64, qs, lds);
             if (b >= (c->djs_tile > 0 ? 1 : 2)) {
-                c->djs_cfg = DjsLaunch{W, qs, nas, lds, ncu * b};
+                c->djs_cfg = DjsLaunch{W, qs, lds, ncu * b};
                 break;
             }
         }
     }
     c->jac_ok = bestW > 0;
-    c->jac_cfg.W = bestW;
-    c->jac_cfg.lds = bestW > 0 ? jacobian_lds_bytes(P, bestW, st64) : 0;
+    // an explicit "jac_tile" asks for the kernel with that tile
+    c->eb_cfg = EdgeBlocksLaunch{};
+    if (c->jac_tile == 0 && !c->inline_radial) (void)eb_plan(Pb, f64, ar64, &c->eb_cfg);
+    // the radial pass's table, at the staging precision
+    P.rtab = nullptr;
+    P.rtab_k = radial_table_intervals(P, st64);
+    if (P.rtab_k > 0 && (reads_radial(c, 0) || reads_radial(c, 1))) {
+        const int kind = st64 ? 8 : 4;
+        if (c->rtab_kind != kind) {
+            c->rtab_kind = 0;
+            hipError_t e = c->b_rtab.ensure(radial_table_bytes(P, st64));
+            if (e == hipSuccess) e = build_radial_table(P, st64, c->b_rtab.p);
+            if (e != hipSuccess) return hip_fail(c, e, "radial table");
+            c->rtab_kind = kind;
+        }
+        P.rtab = c->b_rtab.p;
+        P.rtab_inv_h = (double)P.rtab_k / c->r_cut;
+    }
     return SOAP_OK;
 }
 
@@ -437,6 +491,51 @@ int upload_constants(soap_ctx *c) {
             for (int k = 2; k <= l - m; ++k) v /= (long double)k;
             Nt[(size_t)l * ldN + m] = (double)v;
         }
+    // the edge Jacobian's matrix-core rows: row comp of harmonic (l, m) as
+    // alpha Y[p] + beta Y[q] of harmonics Y (Y[L] = 0), the gradient identities
+    // written out per signed m (see stage_edges)
+    const int Ll = lw * lw, Lp = Ll + 3;
+    std::vector<double> jab(6 * (size_t)Lp, 0.0);
+    std::vector<uint16_t> jpq(4 * (size_t)Lp, 0);
+    for (int l = 0; l < lw; ++l)
+        for (int m = -l; m <= l; ++m) {
+            const int lm = l * l + l + m, mm = m < 0 ? -m : m, lp = l - 1;
+            const double *gcl = gcoef.data() + 4 * (size_t)(l * (l + 1) / 2 + mm);
+            const double cA = gcl[0], cB = gcl[1], cC = gcl[2];
+            // (coefficient, order) pairs per component; order out of degree l - 1: no term
+            double a[4] = {1.0, -cA, 0.0, cC}, b[2] = {0.0, 0.0};
+            int pk[4] = {0, 0, 0, m}, qk[2] = {0, 0};
+            if (m == 0) {
+                a[2] = -cA;
+                pk[1] = 1;
+                pk[2] = -1;
+            } else if (m > 0) {
+                a[2] = -cA;
+                pk[1] = m + 1; b[0] = cB; qk[0] = m - 1;
+                pk[2] = -(m + 1); b[1] = m > 1 ? -cB : 0.0; qk[1] = -(m - 1);
+            } else {
+                a[2] = cA;
+                pk[1] = -(mm + 1); b[0] = mm > 1 ? cB : 0.0; qk[0] = -(mm - 1);
+                pk[2] = mm + 1; b[1] = cB; qk[1] = mm - 1;
+            }
+            auto at = [&](int k, double *cf) -> int { // slot of S_{l-1,k}, or the zero slot
+                if (lp < 0 || k < -lp || k > lp) {
+                    *cf = 0.0;
+                    return Ll;
+                }
+                return lp * lp + lp + k;
+            };
+            for (int d = 0; d < 4; ++d) {
+                const int p = d == 0 ? lm : at(pk[d], &a[d]);
+                const int q = (d == 1 || d == 2) ? at(qk[d - 1], &b[d - 1]) : Ll;
+                jab[(size_t)d * Lp + lm] = a[d];
+                jpq[(size_t)d * Lp + lm] = (uint16_t)(p | q << 8);
+            }
+            jab[4 * (size_t)Lp + lm] = b[0];
+            jab[5 * (size_t)Lp + lm] = b[1];
+        }
+    for (int d = 0; d < 4; ++d) // past the last harmonic: zero rows
+        for (int k = Ll; k < Lp; ++k) jpq[(size_t)d * Lp + k] = (uint16_t)(Ll | Ll << 8);
     // one constant buffer: betaC | betaCa | aprime | remainders of betaC, aprime | G | rq | WN | c0 | Nt | gcoef |
     // exp2 table
     std::vector<double> all;
@@ -455,6 +554,9 @@ int upload_constants(soap_ctx *c) {
     soap_exp2_table64(e2t);
     while (all.size() % 2) all.push_back(0.0); // 16-byte aligned pairs
     size_t o_e2 = all.size(); all.insert(all.end(), e2t, e2t + 128);
+    size_t o_ja = all.size(); all.insert(all.end(), jab.begin(), jab.end());
+    size_t o_jp = all.size(); all.resize(o_jp + (jpq.size() + 3) / 4);
+    std::memcpy(all.data() + o_jp, jpq.data(), 2 * jpq.size());
     hipError_t e;
     if ((e = c->d_const.ensure(all.size() * 8)) != hipSuccess) return hip_fail(c, e, "hipMalloc(constants)");
     if ((e = hipMemcpy(c->d_const.p, all.data(), all.size() * 8, hipMemcpyHostToDevice)) != hipSuccess)
@@ -501,8 +603,11 @@ int upload_constants(soap_ctx *c) {
     P.Nt = d + o_Nt;
     P.gcoef = d + o_gc;
     P.e2t = d + o_e2;
+    P.jab = d + o_ja;
+    P.jpq = reinterpret_cast<const uint16_t *>(d + o_jp);
     P.dtab = c->d_dtab.as<uint32_t>();
     P.tri_lw = (int)c->dtab.size();
+    c->rtab_kind = 0; // of the previous constants
     return plan_launches(c);
 }
 
@@ -574,15 +679,39 @@ size_t scratch_bytes_per_center(const soap_ctx *c) {
     return elt * 4 * (size_t)c->P.S * c->P.n * c->P.L;
 }
 
-// the radial pass (polynomial quadrature): bytes for the edges of centers [first, first + count)
-size_t radial_bytes(const soap_ctx *c, int64_t first, int64_t count) {
-    if (c->P.rbf != 1 || count == 0 || c->h_row.size() != (size_t)c->nc + 1) return 0;
-    return radial_bytes_per_edge(c->P) * (size_t)(c->h_row[first + count] - c->h_row[first]);
+// whether a density mode (and the edge Jacobian kernel after mode 1) reads the
+// radial pass's factors: the Jacobian path but for inline_radial's bases, and
+// the quadrature in every mode
+bool reads_radial(const soap_ctx *c, int mode) {
+    return (mode == 1 && !c->inline_radial) || c->P.rbf == RBF_BUFFERED;
+}
+size_t radial_bytes_per_edge(const soap_ctx *c) {
+    return radial_bytes_per_edge(c->P, c->dtype == SOAP_FP64 || c->ar64);
+}
+size_t block_bytes(const soap_ctx *c) { return (c->dtype == SOAP_FP64 ? 8 : 4) * 3 * (size_t)c->Fe; }
+// whether an edge's Jacobian block holds its radial factors until it is
+// written (all bases but one radial function of one species in float64
+// arithmetic with float32 outputs)
+bool radial_in_place(const soap_ctx *c) { return block_bytes(c) >= radial_bytes_per_edge(c); }
+// most edges that the rows of `count` centers can have
+int64_t edges_bound(const soap_ctx *c, int64_t count) { return std::min(c->E, count * (int64_t)c->maxdeg); }
+
+// The polynomial quadrature's share of a batch's memory (float64 pairs of
+// every edge), which the batch plan and the limit of
+// soap_derivatives_batch_noalloc count: bytes for the edges of centers
+// [first, first + count).
+size_t quad_bytes_per_edge(const soap_ctx *c) {
+    return c->P.rbf == RBF_BUFFERED ? 16 * (size_t)c->P.n * (c->P.lmax + 1) : 0;
+}
+size_t quad_bytes(const soap_ctx *c, int64_t first, int64_t count) {
+    if (count == 0 || c->h_row.size() != (size_t)c->nc + 1) return 0;
+    return quad_bytes_per_edge(c) * (size_t)(c->h_row[first + count] - c->h_row[first]);
 }
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 Params params_for(const soap_ctx *c, int mode) {
     Params P = c->P;
+    if (reads_radial(c, mode)) P.rbf = RBF_BUFFERED;
     const int G = c->groups[mode];
     P.n_groups = G;
     for (int k = 0; k <= G; ++k) P.lgrp[k] = c->lgrp[mode][k];
@@ -746,8 +875,8 @@ int soap_get_option(const soap_ctx *c, const char *key, int64_t *value) {
                {"jacobian_density_lds", (int64_t)(c->djac_cfg.W > 0 ? c->djac_cfg.lds
                                                                     : (c->djs_cfg.W > 0 ? c->djs_cfg.lds
                                                                                         : c->dens_cfg[1].lds))},
-               {"jacobian_tile", c->jac_cfg.W},
-               {"jacobian_lds", (int64_t)c->jac_cfg.lds},
+               {"jacobian_tile", c->eb_cfg.threads > 0 ? 4 * c->eb_cfg.Q : c->jac_cfg.W},
+               {"jacobian_lds", (int64_t)(c->eb_cfg.threads > 0 ? c->eb_cfg.lds : c->jac_cfg.lds)},
                {"output_lds", (int64_t)c->out_plan.lds},
                {"descriptor_kernel", c->desc_cfg.W > 0 ? 1 : 0},
                // 0 k_density, 1 k_djac, 2 k_djs (then the output kernel)
@@ -839,8 +968,9 @@ static int build_rows(soap_ctx *c, int64_t n_atoms, int64_t center_bound, const 
     const int64_t cap0 = c->b_cols.p ? (int64_t)(c->b_cols.cap / 4) : 0;
     if (cap0 > 0 && (e = nbr_pack(w, n_centers, row, c->b_cols.as<int32_t>(), cap0, st)) != hipSuccess)
         return hip_fail(c, e, "neighbour rows");
-    // The polynomial quadrature's radial pass places each call's edges from a
-    // host copy of the row offsets: copied with the flags, one synchronisation.
+    // soap_derivatives_batch_noalloc's limit counts the polynomial quadrature's
+    // edges from a host copy of the row offsets: copied with the flags, one
+    // synchronisation.
     c->h_row.clear();
     const bool rows_to_host = c->rbf == SOAP_RBF_POLYNOMIAL;
     if (rows_to_host) {
@@ -906,6 +1036,7 @@ static int build_rows(soap_ctx *c, int64_t n_atoms, int64_t center_bound, const 
     e = nbr_phase2(w, n_atoms, pos_dev, f64, n_centers, centers_dev, c->r_cut, row, n_long > 0, packed,
                    c->b_cols.as<int32_t>(), (int64_t)(c->b_cols.cap / 4), st);
     if (e != hipSuccess) return hip_fail(c, e, "neighbour rows");
+    c->maxdeg = maxdeg;
     *E_out = E;
     return SOAP_OK;
 }
@@ -980,6 +1111,10 @@ int soap_build_neighbors(soap_ctx *c, int64_t n_atoms, const void *pos_dev, cons
     if ((rc = build_rows(c, n_rows_atoms, n_atoms, pos_rows, Z_rows, n_centers, cen_rows, &E, st)) != SOAP_OK)
         return rc;
     timer.done();
+    if (!radial_in_place(c)) {
+        hipError_t e = c->b_radial.ensure(radial_bytes_per_edge(c) * (size_t)E);
+        if (e != hipSuccess) return hip_fail(c, e, "hipMalloc(radial factors)");
+    }
     c->have_rows = true;
     c->n_atoms = n_atoms;
     c->n_ext = n_rows_atoms;
@@ -1069,25 +1204,31 @@ static bool jacobian_path_ok(const soap_ctx *c, int mode) {
     return c->dens_ok[mode] && (mode != 1 || (c->jac_ok && (c->groups[1] == 1 || c->out_ok)));
 }
 
-// The polynomial quadrature's radial factors (B_nl, Bh_nl) of the edges of
-// centers [first, first + count), evaluated once per call by k_radial into
-// buf (NULL = the context's buffer, grown as needed) and read by every
-// kernel of the call through P.rad.  Nothing to do for the other bases.
-static int prepare_radial(soap_ctx *c, int64_t first, int64_t count, void *buf, hipStream_t st) {
-    c->P.rad = nullptr;
-    c->P.rad_e0 = 0;
-    if (c->P.rbf != 1 || count == 0) return SOAP_OK;
-    if (c->h_row.size() != (size_t)c->nc + 1) return fail(c, SOAP_ESTATE, "neighbour row offsets missing");
-    if (!buf) {
-        hipError_t e = c->b_radial.ensure(radial_bytes(c, first, count));
+// The radial factors (B_nl, Bh_nl) of the edges of centers [first, first +
+// count), for the kernels of one call, which find them through P.rad.  On the
+// Jacobian path (jac_edge, the blocks of the edges from center `origin` on)
+// the factors of an edge go to the start of the edge's own block: the kernels
+// read them from there, k_jacobian last, before it writes the block, so the
+// call needs no memory for them.  Where a block is too short (allocated with
+// the neighbour list, so that soap_derivatives_batch_noalloc finds it), and
+// for the quadrature's other modes, the context's buffer takes them.
+static int prepare_radial(soap_ctx *c, int mode, int64_t first, int64_t count, void *jac_edge, int64_t origin,
+                          hipStream_t st) {
+    const size_t per = radial_bytes_per_edge(c), block = block_bytes(c);
+    const int64_t n = edges_bound(c, count);
+    const bool in_place = mode == 1 && jac_edge && radial_in_place(c);
+    c->P.rad = in_place ? jac_edge : nullptr;
+    c->P.rad_stride = (int64_t)(in_place ? block : per);
+    c->P.rad_origin = c->b_row.as<int64_t>() + (in_place ? origin : first);
+    if (n == 0 || (mode == 1 && !jac_edge)) return SOAP_OK; // no edges
+    if (!in_place) {
+        hipError_t e = c->b_radial.ensure(per * (size_t)n);
         if (e != hipSuccess) return hip_fail(c, e, "hipMalloc(radial factors)");
-        buf = c->b_radial.p;
+        c->P.rad = c->b_radial.p;
     }
-    const int64_t e0 = c->h_row[first];
-    hipError_t e = launch_radial(c->P, rows_of(c, first, count), c->pos, c->built_f64, e0, buf, st);
+    hipError_t e = launch_radial(c->P, rows_of(c, first, count), c->pos, c->built_f64, c->ar64,
+                                 (double)c->E / (double)c->nc, st);
     if (e != hipSuccess) return hip_fail(c, e, "radial kernel");
-    c->P.rad = (const double2 *)buf;
-    c->P.rad_e0 = e0;
     return SOAP_OK;
 }
 
@@ -1098,25 +1239,25 @@ static int prepare_radial(soap_ctx *c, int64_t first, int64_t count, void *buf, 
 // (NULL = the context's, grown as needed).
 // timed = false: no timer events (they may allocate).  wg_per_cu > 0 caps
 // the persistent density kernel's workgroups per CU.
+// jc_edge: the edge blocks of modes 1 and 2, from center `origin` on (-1: first).
 static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void *desc, void *c_out, void *jself,
                        void *jc_edge, void *scratch, void *stream, bool timed = true, int wg_per_cu = 0,
-                       bool prep_radial = true) {
+                       int64_t origin = -1) {
     if (!c->have_rows) return fail(c, SOAP_ESTATE, "no neighbour list: call soap_build_neighbors first");
     int rc;
     if ((rc = check_ctx_device(c)) != SOAP_OK) return rc;
     if (!jacobian_path_ok(c, mode))
         return fail(c, SOAP_EINVAL, "basis too large for the on-chip memory of the %s kernels",
                     mode == 2 ? "coefficient Jacobian" : "Jacobian");
-    // a caller-given scratch also holds the radial factors, after the coefficients
-    void *rbuf = (scratch && mode == 1) ? (char *)scratch + align256(scratch_bytes_per_center(c) * (size_t)count)
-                                        : nullptr;
+    if (origin < 0) origin = first;
     if (mode == 1 && !scratch) {
         hipError_t e = c->b_cscratch.ensure(scratch_bytes_per_center(c) * (size_t)count);
         if (e != hipSuccess) return hip_fail(c, e, "hipMalloc(coefficient scratch)");
         scratch = c->b_cscratch.p;
     }
     SegTimer timer(c, 1, to_stream(stream), timed);
-    if (prep_radial && (rc = prepare_radial(c, first, count, rbuf, to_stream(stream))) != SOAP_OK) return rc;
+    if (reads_radial(c, mode) && (rc = prepare_radial(c, mode, first, count, jc_edge, origin, to_stream(stream))) != SOAP_OK)
+        return rc;
     const Params P = params_for(c, mode);
     if (mode == 0 && c->desc_cfg.W > 0) { // one wave per center
         hipError_t e = launch_desc(P, rows_of(c, first, count), c->pos, c->built_f64, c->ar64, c->desc_cfg, desc, c_out,
@@ -1159,7 +1300,7 @@ static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void
         (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
         cfg.blocks = std::max(1, std::min(cfg.blocks, ncu * wg_per_cu / std::max(1, P.n_groups)));
     }
-    hipError_t e = launch_density(P, rows_of(c, first, count), c->pos, c->built_f64, c->ar64, mode, cfg,
+    hipError_t e = launch_density(P, rows_part(c, origin, first, count), c->pos, c->built_f64, c->ar64, mode, cfg,
                                   c->nw.work, &c->work_epoch, desc, c_out, jself, scratch, jc_edge, to_stream(stream));
     if (e != hipSuccess) return hip_fail(c, e, "density kernel");
     if (mode == 1 && P.n_groups > 1) { // with one l-group the density kernel writes desc and jself
@@ -1225,6 +1366,16 @@ int soap_compute_averaged(soap_ctx *c, int32_t mode, void *desc_dev, void *strea
     return SOAP_OK;
 }
 
+// the edge blocks of centers [cf, cf + cn) of the output batch from `first`
+static hipError_t run_jacobian(const soap_ctx *c, int64_t first, int64_t cf, int64_t cn, const void *scratch,
+                               void *jac_edge, hipStream_t st) {
+    const Params P = params_for(c, 1);
+    const Rows R = rows_part(c, first, cf, cn);
+    if (c->eb_cfg.threads > 0)
+        return launch_edge_blocks(P, R, c->pos, c->built_f64, c->ar64, c->eb_cfg, scratch, jac_edge, st);
+    return launch_jacobian(P, R, c->pos, c->built_f64, c->ar64, c->jac_cfg, scratch, jac_edge, st);
+}
+
 // Pipelined descriptor + Jacobian: the batch in K center chunks; the density
 // kernel of each chunk on `stream`, the Jacobian kernel of the chunk on the
 // context's second stream once the chunk's coefficients are in scratch, so
@@ -1243,27 +1394,20 @@ static int run_derivatives_pipelined(soap_ctx *c, int64_t first, int64_t count, 
     if (e == hipSuccess) e = c->b_cscratch.ensure(scratch_bytes_per_center(c) * (size_t)count);
     if (e != hipSuccess) return hip_fail(c, e, "pipelined derivatives (setup)");
     char *scratch = (char *)c->b_cscratch.p;
-    { // the radial factors of every chunk at once: the chunks' Jacobian launches read them on the other stream
-        SegTimer timer(c, 1, st);
-        const int rc = prepare_radial(c, first, count, nullptr, st);
-        if (rc != SOAP_OK) return rc;
-        timer.done();
-    }
     const size_t elt = c->built_f64 ? 8 : 4, pc = scratch_bytes_per_center(c);
     for (int k = 0; k < K; ++k) {
         const int64_t cf = first + count * k / K, cn = first + count * (k + 1) / K - cf;
         if (cn == 0) continue;
         const size_t o = (size_t)(cf - first);
         int rc = run_density(c, 1, cf, cn, (char *)desc_dev + o * c->F * elt, nullptr,
-                             (char *)jac_self_dev + o * 3 * c->F * elt, nullptr, scratch + o * pc, stream, true,
-                             c->pipe_density_wg, false);
+                             (char *)jac_self_dev + o * 3 * c->F * elt, jac_edge_dev, scratch + o * pc, stream, true,
+                             c->pipe_density_wg, first);
         if (rc != SOAP_OK) return rc;
         if ((e = hipEventRecord(c->pipe_ev[k], st)) != hipSuccess ||
             (e = hipStreamWaitEvent(c->aux, c->pipe_ev[k], 0)) != hipSuccess)
             return hip_fail(c, e, "pipelined derivatives (events)");
         SegTimer timer(c, 2, c->aux);
-        e = launch_jacobian(c->P, rows_part(c, first, cf, cn), c->pos, c->built_f64, c->ar64, c->jac_cfg,
-                            scratch + o * pc, jac_edge_dev, c->aux);
+        e = run_jacobian(c, first, cf, cn, scratch + o * pc, jac_edge_dev, c->aux);
         if (e != hipSuccess) return hip_fail(c, e, "Jacobian kernel");
         timer.done();
     }
@@ -1275,21 +1419,22 @@ static int run_derivatives_pipelined(soap_ctx *c, int64_t first, int64_t count, 
 
 // descriptor + Jacobian of the centers [first, first + count) in consecutive
 // batches of at most B centers, one after another on `stream`: the density
-// step and the Jacobian kernel of each batch, the coefficient scratch (and the
-// polynomial radial factors) sized for one batch.  Every output is indexed
-// from `first`, as in one call (the edge blocks through Rows::e_origin).
+// step and the Jacobian kernel of each batch, the coefficient scratch sized
+// for one batch (scratch: as run_density).  Every output
+// is indexed from `first`, as in one call (the edge blocks through
+// Rows::e_origin).
 static int run_derivatives_batched(soap_ctx *c, int64_t first, int64_t count, int64_t B, void *desc_dev,
-                                   void *jac_edge_dev, void *jac_self_dev, void *stream) {
+                                   void *jac_edge_dev, void *jac_self_dev, void *scratch, void *stream, bool timed) {
     const size_t elt = c->built_f64 ? 8 : 4;
     for (int64_t cf = first; cf < first + count; cf += B) {
         const int64_t cn = std::min(B, first + count - cf), o = cf - first;
         int rc = run_density(c, 1, cf, cn, (char *)desc_dev + o * c->F * elt, nullptr,
-                             (char *)jac_self_dev + o * 3 * c->F * elt, nullptr, nullptr, stream);
+                             (char *)jac_self_dev + o * 3 * c->F * elt, jac_edge_dev, scratch, stream, timed, 0, first);
         if (rc != SOAP_OK) return rc;
         if (c->E == 0) continue;
-        SegTimer timer(c, 2, to_stream(stream));
-        hipError_t e = launch_jacobian(c->P, rows_part(c, first, cf, cn), c->pos, c->built_f64, c->ar64, c->jac_cfg,
-                                       c->b_cscratch.p, jac_edge_dev, to_stream(stream));
+        SegTimer timer(c, 2, to_stream(stream), timed);
+        hipError_t e = run_jacobian(c, first, cf, cn, scratch ? scratch : c->b_cscratch.p, jac_edge_dev,
+                                    to_stream(stream));
         if (e != hipSuccess) return hip_fail(c, e, "Jacobian kernel");
         timer.done();
     }
@@ -1300,33 +1445,19 @@ static int run_derivatives_batched(soap_ctx *c, int64_t first, int64_t count, in
 static int run_derivatives(soap_ctx *c, int64_t first, int64_t count, void *desc_dev, void *jac_edge_dev,
                            void *jac_self_dev, void *scratch, void *stream, bool timed = true) {
     if (count == 0) return SOAP_OK;
-    if (timed && !scratch && c->batch_centers > 0 && count > c->batch_centers) {
-        int rc;
-        if (!jacobian_path_ok(c, 1))
-            return fail(c, SOAP_EINVAL, "basis too large for the on-chip memory of the Jacobian kernels");
-        if ((rc = check_ctx_device(c)) != SOAP_OK) return rc;
-        return run_derivatives_batched(c, first, count, c->batch_centers, desc_dev, jac_edge_dev, jac_self_dev,
-                                       stream);
-    }
+    int rc;
+    if ((rc = check_ctx_device(c)) != SOAP_OK) return rc;
+    if (!jacobian_path_ok(c, 1))
+        return fail(c, SOAP_EINVAL, "basis too large for the on-chip memory of the Jacobian kernels");
+    const bool batched = timed && !scratch && c->batch_centers > 0 && count > c->batch_centers;
     // the pipelined path needs its own stream, events and the context's
     // scratch: not for the allocation-free entry point
-    if (timed && !scratch && c->pipe_chunks > 1 && c->E > 0 && count >= 2 * c->pipe_chunks) {
-        int rc;
-        if (!jacobian_path_ok(c, 1))
-            return fail(c, SOAP_EINVAL, "basis too large for the on-chip memory of the Jacobian kernels");
-        if ((rc = check_ctx_device(c)) != SOAP_OK) return rc;
+    if (!batched && timed && !scratch && c->pipe_chunks > 1 && c->E > 0 && count >= 2 * c->pipe_chunks &&
+        radial_in_place(c)) // the chunks' factors side by side
         return run_derivatives_pipelined(c, first, count, c->pipe_chunks, desc_dev, jac_edge_dev, jac_self_dev,
                                          stream);
-    }
-    int rc = run_density(c, 1, first, count, desc_dev, nullptr, jac_self_dev, nullptr, scratch, stream, timed);
-    if (rc != SOAP_OK) return rc;
-    if (c->E == 0) return SOAP_OK;
-    SegTimer timer(c, 2, to_stream(stream), timed);
-    hipError_t e = launch_jacobian(c->P, rows_of(c, first, count), c->pos, c->built_f64, c->ar64, c->jac_cfg,
-                                   scratch ? scratch : c->b_cscratch.p, jac_edge_dev, to_stream(stream));
-    if (e != hipSuccess) return hip_fail(c, e, "Jacobian kernel");
-    timer.done();
-    return SOAP_OK;
+    return run_derivatives_batched(c, first, count, batched ? c->batch_centers : count, desc_dev, jac_edge_dev,
+                                   jac_self_dev, scratch, stream, timed);
 }
 
 int soap_derivatives(soap_ctx *c, void *desc_dev, void *jac_edge_dev, void *jac_self_dev, void *stream) {
@@ -1370,12 +1501,12 @@ int soap_derivatives_batch_noalloc(soap_ctx *c, int64_t first, int64_t count, vo
     if (rc != SOAP_OK) return rc;
     if (count > 0 && (!desc_dev || !jac_self_dev || !jac_edge_dev))
         return fail(c, SOAP_EINVAL, "output pointer is NULL");
-    const size_t need = align256(scratch_bytes_per_center(c) * (size_t)count) + radial_bytes(c, first, count);
+    const size_t need = align256(scratch_bytes_per_center(c) * (size_t)count) + quad_bytes(c, first, count);
     if (need > (size_t)SOAP_STATIC_SCRATCH_BYTES)
         return fail(c, SOAP_ECAPACITY,
                     "%lld centers need %zu bytes of coefficient scratch%s, above the static %d bytes (at most %lld "
                     "centers per call for this basis)",
-                    (long long)count, need, c->P.rbf == 1 ? " and radial factors" : "", SOAP_STATIC_SCRATCH_BYTES,
+                    (long long)count, need, c->P.rbf == RBF_BUFFERED ? " and radial factors" : "", SOAP_STATIC_SCRATCH_BYTES,
                     (long long)(SOAP_STATIC_SCRATCH_BYTES / scratch_bytes_per_center(c)));
     if (!c->static_scratch) return fail(c, SOAP_EHIP, "the static scratch of device %d is not available", c->device);
     // the density kernel writes every scratch entry the later kernels read,
@@ -1398,7 +1529,7 @@ int soap_plan_batches(soap_ctx *c, int32_t what, int64_t budget_bytes, int64_t m
     // per center: descriptor row (+ center block and coefficient scratch);
     // per edge: its neighbour block
     const int64_t per_center = (int64_t)(elt * c->F * (jac ? 4 : 1) + (jac ? scratch_bytes_per_center(c) : 0));
-    const int64_t per_edge = (jac ? (int64_t)(elt * 3 * c->Fe) : 0) + (c->P.rbf == 1 ? (int64_t)radial_bytes_per_edge(c->P) : 0);
+    const int64_t per_edge = (jac ? (int64_t)(elt * 3 * c->Fe) : 0) + (int64_t)quad_bytes_per_edge(c);
     int64_t nb = 0, b0 = 0;
     while (b0 < c->nc) {
         int64_t b1 = b0, bytes = 0;
@@ -1474,7 +1605,7 @@ void soap_destroy(soap_ctx *c) {
     (void)hipDeviceSynchronize();
     for (DevBuf *b : {&c->d_const, &c->d_dtab, &c->d_fmap, &c->d_lut, &c->b_zero, &c->b_bstart, &c->b_acell,
                       &c->b_srec, &c->b_sspec, &c->b_deg, &c->b_slots, &c->b_scan, &c->b_spec, &c->b_row, &c->b_cols,
-                      &c->b_cscratch, &c->b_avg, &c->b_avg_part, &c->b_img_lohi, &c->b_img_cnt, &c->b_img_start,
+                      &c->b_cscratch, &c->b_radial, &c->b_rtab, &c->b_avg, &c->b_avg_part, &c->b_img_lohi, &c->b_img_cnt, &c->b_img_start,
                       &c->b_pos_ext, &c->b_Z_ext, &c->b_map_atom, &c->b_map_img, &c->b_iota})
         b->release();
     if (c->h_flags) (void)hipHostFree(c->h_flags);

@@ -1,4 +1,4 @@
-// The float32 Jacobian kernel compiled for fixed (n_max, l_max + 1) pairs:
+// The float32 Jacobian kernel of the GTO basis compiled for fixed (n_max, l_max + 1) pairs:
 // with the basis dimensions known to the compiler, its index arithmetic and
 // loop bounds fold into constants.  Built once per part (JF_PART = 0, 1, 2)
 // so the parts compile in parallel; each part answers for its n_max values.
@@ -14,7 +14,7 @@
 namespace soap {
 
 #define JF_CASE(N, LW)                                                                                             \
-    if (n == N && lw == LW) return reinterpret_cast<const void *>(&dev::k_jacobian<float, float, N, LW>);
+    if (n == N && lw == LW) return reinterpret_cast<const void *>(&dev::k_jacobian<float, float, N, LW, 0>);
 #define JF_ROW(N) JF_CASE(N, 3) JF_CASE(N, 5) JF_CASE(N, 7) JF_CASE(N, 9) JF_CASE(N, 11) JF_CASE(N, 13)
 
 const void *JF_CAT(jacobian_fixed_, JF_PART)(int n, int lw) {

@@ -60,6 +60,28 @@ template <> struct Pair<float> {
     static __device__ __forceinline__ float2 make(double a, double b) { return make_float2((float)a, (float)b); }
 };
 
+// The radial pass's pairs of one edge (P.rad): 4-byte aligned, as they may
+// lie at the start of the edge's Jacobian block, whose length is any number
+// of values.
+template <typename T> struct __attribute__((packed, aligned(4))) RadPair {
+    T b, h;
+};
+template <typename T> __device__ __forceinline__ RadPair<T> *rad_row(const Params &P, int64_t e) {
+    return (RadPair<T> *)((char *)P.rad + e * P.rad_stride);
+}
+template <typename T> __device__ __forceinline__ typename Pair<T>::type load_pair(const RadPair<T> *p, int t) {
+    typename Pair<T>::type v;
+    v.x = p[t].b;
+    v.y = p[t].h;
+    return v;
+}
+template <typename T> __device__ __forceinline__ void store_pair(RadPair<T> *p, int t, double b, double h) {
+    RadPair<T> v;
+    v.b = (T)b;
+    v.h = (T)h;
+    p[t] = v;
+}
+
 // four consecutive LDS values (16-byte aligned) as float64
 __device__ __forceinline__ void load4(const double *p, double &a, double &b, double &c, double &d) {
     const double2 u = *(const double2 *)p, v = *(const double2 *)(p + 2);
@@ -423,7 +445,7 @@ __device__ __forceinline__ void lds_barrier() {
 //   YY: harmonics, element (edge e, component c, lm) at
 //       e es + c cs + (lm - lmY0) ls; component 0 = S, 1..3 = dS/dx_d (GRAD).
 //       Degrees from lgY0 = lg0 - 1 (GRAD and lg0 > 0) or lg0 are stored.
-//   BB[e][n][lc] = K (B_nl, Bh_nl), K = K_l if scaleK else 1, stored at precision BT
+//   BB[e][n][lc] = (B_nl, Bh_nl), stored at precision BT
 //   X: GTO exponentials [e][k][lc], the polynomial table [e][q][0..lg1], or
 //      the Laplace form's P_j [e][n][j]
 // Phase 1 runs the harmonic columns (edge, m), then the radial scratch;
@@ -446,7 +468,7 @@ template <bool GRAD, typename BT = double, int NT = 0, int LWT = 0, typename YT 
 __device__ __forceinline__ void stage_edges(const Params &P, const Tables &T, YT *__restrict__ YY, YLayout yl,
                                             typename Pair<BT>::type *__restrict__ BB, double *__restrict__ X,
                                             const double *__restrict__ geo, int nb, int lane, int lg0, int lg1,
-                                            bool scaleK, int64_t r0) {
+                                            int64_t r0) {
     const int n = NT ? NT : P.n, ldN = (LWT ? LWT - 1 : P.lmax) + 2, lgc = lg1 - lg0, nlc = n * lgc;
     const int lgY0 = (GRAD && lg0 > 0) ? lg0 - 1 : lg0;
     const float inv_lg1 = 1.0f / (float)lg1, inv_nlc = 1.0f / (float)nlc, inv_lgc = 1.0f / (float)lgc;
@@ -560,8 +582,7 @@ __device__ __forceinline__ void stage_edges(const Params &P, const Tables &T, YT
                 cb += (fma(c.x, eh, -pb) + tb.lo) + (c.x * el + c.y * eh);
                 ch += (fma(m.hi, eh, -ph) + th.lo) + (m.hi * el + m.lo * eh);
             }
-            const double K = scaleK ? T.Kl[lg0 + lc] : 1.0;
-            BB[it] = Pair<BT>::make(K * (sb + cb), -2.0 * K * (sh + ch));
+            BB[it] = Pair<BT>::make(sb + cb, -2.0 * (sh + ch));
         }
     } else if (rbf == 0) {
         for (int it = lane; it < nd; it += 128) {
@@ -580,9 +601,8 @@ __device__ __forceinline__ void stage_edges(const Params &P, const Tables &T, YT
                 b2 += c2.x * v2;
                 h2 += c2.y * v2;
             }
-            const double K1 = scaleK ? T.Kl[lg0 + l1] : 1.0, K2 = scaleK ? T.Kl[lg0 + l2] : 1.0;
-            BB[it] = Pair<BT>::make(K1 * b1, K1 * h1);
-            BB[i2] = Pair<BT>::make(K2 * b2, K2 * h2);
+            BB[it] = Pair<BT>::make(b1, h1);
+            BB[i2] = Pair<BT>::make(b2, h2);
         }
     } else if (rbf == 2) {
         // Laplace form, u = r_cut - r, k = 1..n: the bracket of Eq. (poly-coefficients) summed over k
@@ -610,18 +630,14 @@ __device__ __forceinline__ void stage_edges(const Params &P, const Tables &T, YT
                 b = rl * f;
                 bh = rl * ir * (fp - (double)l * f * ir);
             }
-            const double K = scaleK ? T.Kl[l] : 1.0;
-            BB[it] = Pair<BT>::make(K * b, K * bh);
+            BB[it] = Pair<BT>::make(b, bh);
         }
     } else {
-        // polynomial quadrature: the factors k_radial left for this call's edges, [edge][n][l]
+        // the factors the radial pass left for this call's edges (r0: the first, from *P.rad_origin)
         const int lwa = P.lmax + 1;
-        const double2 *rad = P.rad + (r0 - P.rad_e0) * (size_t)n * lwa + lg0;
         for (int it = lane; it < nd; it += 64) {
             const int e = qdiv(it, inv_nlc), t = it - e * nlc, a = qdiv(t, inv_lgc), lc = t - a * lgc;
-            const double2 v = rad[((size_t)e * n + a) * lwa + lc];
-            const double K = scaleK ? T.Kl[lg0 + lc] : 1.0;
-            BB[it] = Pair<BT>::make(K * v.x, K * v.y);
+            BB[it] = load_pair<BT>(rad_row<BT>(P, r0 + e), a * lwa + lg0 + lc);
         }
     }
     wave_sync();
@@ -642,130 +658,6 @@ __device__ __forceinline__ void load_rows(double *geo, int *sp, const PosT *__re
         geo[4 * t + 2] = z;
         geo[4 * t + 3] = sqrt(x * x + y * y + z * z);
         sp[t] = spec[j];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// k_radial: the polynomial basis's radial factors of every edge of a range of
-// centers, evaluated once per call and read by every density and Jacobian
-// kernel (quadrature form of the radial integral, Sec. 2.3: the sums over the
-// basis and over the nodes swapped, G[n][q] = w_q r_q^2 g_n(r_q) 4 pi):
-//   B_nl  = r^-l sum_q G_nq ii_l(x_q) g_q,
-//   Bh_nl = (1/r) dB_nl/dr
-//         = r^-l (1/r) sigma^-2 sum_q G_nq (r_q ii_{l+1}(x_q) - r ii_l(x_q)) g_q,
-// x_q = r r_q / sigma^2, g_q = exp(-(r_q - r)^2 / (2 sigma^2)) (ii_l the
-// exponentially scaled modified spherical Bessel function, the derivative
-// from i_l' = i_{l+1} + (l/x) i_l), and for an edge of length 0 only the
-// l = 0 factor, B_n0(0).  Output [edge - e_base][n][l] = (B_nl, Bh_nl) for
-// l <= l_max, unscaled by K_l.
-// A workgroup takes a block of cb consecutive centers, whose edges are
-// contiguous; its waves take four edges at a time, round-robin, each lane
-// finding its edge's center in the block's row offsets.  Per four edges the
-// Bessel values of (edge, node) for 16 nodes at once go to the wave's LDS
-// slab, then lane = (edge, l) accumulates all NA radial indices over those
-// nodes (G broadcast from LDS).  The node sums run in node order, as in the
-// in-kernel evaluation.
-// ---------------------------------------------------------------------------
-constexpr int NWR = 4, BSR = 64 * NWR;
-constexpr int RAD_EC = 4, RAD_QC = 16; // edges per wave pass; nodes per Bessel slab
-constexpr int RAD_CB_MAX = 256;        // centers per workgroup block
-
-__host__ __device__ __forceinline__ int radial_qpad(int Q) { return (Q + RAD_QC - 1) / RAD_QC * RAD_QC; }
-// LDS doubles of k_radial: the block's row offsets [RAD_CB_MAX + 1], G [NA][Qp], r_q [Qp], and
-// per wave the Bessel slab [64][l_max + 2]
-__host__ __device__ __forceinline__ size_t radial_lds_doubles(const Params &P, int na) {
-    const size_t qp = (size_t)radial_qpad(P.Q);
-    return even(RAD_CB_MAX + 1) + even((size_t)na * qp) + even(qp) + NWR * even(64 * ((size_t)P.lmax + 2));
-}
-
-template <typename PosT, int NA>
-__global__ __launch_bounds__(BSR) void k_radial(Params P, Rows R, const PosT *__restrict__ pos, int64_t e_base,
-                                                int cb, double2 *__restrict__ out) {
-    extern __shared__ __align__(16) double smem[];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = P.n, Q = P.Q, Qp = radial_qpad(Q), lw = P.lmax + 1, tw = lw + 1;
-    Carver cv{smem};
-    int64_t *rp = (int64_t *)cv.take(RAD_CB_MAX + 1);
-    double *G = cv.take((size_t)NA * Qp);
-    double *rq = cv.take((size_t)Qp);
-    double *slab = cv.take(0) + (size_t)wave * even(64 * (size_t)tw);
-    for (int k = tid; k < NA * Qp; k += BSR) {
-        const int a = k / Qp, q = k - a * Qp;
-        G[k] = (a < n && q < Q) ? P.G[(size_t)a * Q + q] : 0.0;
-    }
-    for (int k = tid; k < Qp; k += BSR) rq[k] = k < Q ? P.rq[k] : 0.0;
-    const int es = lane >> 4, sub = lane & 15; // edge slot; node (Bessel phase) or l (sum phase)
-    double *mine = slab + (size_t)lane * tw;          // this lane's (edge, node) Bessel row
-    const double *col = slab + (size_t)es * RAD_QC * tw; // this lane's edge, all 16 nodes
-    const int l = sub < lw ? sub : lw - 1;
-    for (int64_t c0 = (int64_t)blockIdx.x * cb; c0 < R.nc; c0 += (int64_t)gridDim.x * cb) {
-        const int ncb = (int)((R.nc - c0) < cb ? (R.nc - c0) : cb);
-        __syncthreads(); // the tables; the previous block's readers of rp
-        for (int t = tid; t <= ncb; t += BSR) rp[t] = R.row_ptr[c0 + t];
-        __syncthreads();
-        const int64_t E1 = rp[ncb];
-        for (int64_t eb = rp[0] + (int64_t)RAD_EC * wave; eb < E1; eb += (int64_t)RAD_EC * NWR) {
-            const int64_t e = eb + es;
-            const bool live = e < E1;
-            double r = 0.0;
-            if (live) {
-                int lo = 0, hi = ncb - 1; // the center of e: the last k with rp[k] <= e
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (rp[mid] <= e) lo = mid;
-                    else hi = mid - 1;
-                }
-                const int64_t ci = c0 + lo;
-                const int64_t i = R.centers ? (int64_t)R.centers[ci] : R.c_base + ci;
-                const int64_t j = R.cols[e];
-                const double x = (double)pos[3 * j] - (double)pos[3 * i], y = (double)pos[3 * j + 1] - (double)pos[3 * i + 1],
-                             z = (double)pos[3 * j + 2] - (double)pos[3 * i + 2];
-                r = sqrt(x * x + y * y + z * z);
-            }
-            double b[NA], h[NA];
-#pragma unroll
-            for (int a = 0; a < NA; ++a) b[a] = h[a] = 0.0;
-            for (int q0 = 0; q0 < Qp; q0 += RAD_QC) {
-                const int q = q0 + sub;
-                if (live && q < Q) {
-                    const double xq = rq[q];
-                    const double gq = exp(-0.5 * (xq - r) * (xq - r) * P.inv_s2);
-                    bessel_scaled_lds(lw, xq * r * P.inv_s2, gq, mine);
-                } else {
-                    for (int k = 0; k < tw; ++k) mine[k] = 0.0;
-                }
-                wave_sync();
-#pragma unroll 2
-                for (int qq = 0; qq < RAD_QC; ++qq) {
-                    const double tl = col[qq * tw + l], d = rq[q0 + qq] * col[qq * tw + l + 1] - r * tl;
-                    const double *g = G + q0 + qq;
-#pragma unroll
-                    for (int a = 0; a < NA; ++a) {
-                        const double ga = g[(size_t)a * Qp];
-                        b[a] += ga * tl;
-                        h[a] += ga * d;
-                    }
-                }
-                wave_sync(); // the slab is read before the next nodes overwrite it
-            }
-            if (live && sub < lw) {
-                double sb = 1.0, sh = 0.0;
-                if (r == 0.0) {
-                    sb = l == 0 ? 1.0 : 0.0;
-                } else {
-                    const double ir = 1.0 / r;
-                    double rl = 1.0;
-                    for (int k = 0; k < l; ++k) rl *= ir;
-                    sb = rl;
-                    sh = rl * ir * P.inv_s2;
-                }
-                double2 *o = out + (e - e_base) * (size_t)n * lw + l;
-#pragma unroll
-                for (int a = 0; a < NA; ++a)
-                    if (a < n) o[(size_t)a * lw] = make_double2(b[a] * sb, h[a] * sh);
-            }
-        }
     }
 }
 
@@ -1066,24 +958,22 @@ __host__ __device__ __forceinline__ size_t dens_wave_doubles(const Params &P, in
 
 // MODE: 0 descriptor (c, power spectrum); 1 descriptor + Jacobian (c and D);
 // 2 coefficient Jacobian ("cc": c, every edge's dc/dr_j, and -D).
-// RBF: the radial basis, fixed at compile time (0 GTO, 1 polynomial by
-// quadrature, 2 polynomial in the Laplace form, 3 GTO compensated).  The other bases' branches of
-// the staging then drop out, and with them up to 40 VGPRs: the GTO descriptor
-// kernel runs four waves per SIMD instead of three.
+// RBF: where the radial factors come from, fixed at compile time (1 the radial
+// pass: every basis in mode 1, the polynomial quadrature in the other modes;
+// 0 GTO, 2 polynomial in the Laplace form, 3 GTO compensated: evaluated in
+// the staging of modes 0 and 2).  The other branches of the staging then drop
+// out, and with them up to 40 VGPRs: the GTO descriptor kernel runs four
+// waves per SIMD instead of three.
 // Resident waves per SIMD: a second variant (HI) of the coefficient Jacobian
-// asks for 2 (it otherwise takes all 256 VGPRs and runs one wave), and of the
-// Jacobian path of GTO and the Laplace form for 3 (a small spill).  More
+// asks for 2 (it otherwise takes all 256 VGPRs and runs one wave).  More
 // workgroups per CU split the LDS further, so the host takes HI only where
-// the LDS plan stays as good (density_has_high and plan_launches).
-constexpr bool dens_has_high(int mode, int rbf) { return mode == 2 || (mode == 1 && (rbf == 0 || rbf == 2)); }
-constexpr int dens_min_waves(int mode, int rbf, bool hi) {
-    return (hi && dens_has_high(mode, rbf)) ? (mode == 2 ? 2 : 3) : 1;
-}
+// the LDS plan allows it (plan_launches).
+constexpr int dens_min_waves(int mode, bool hi) { return hi && mode == 2 ? 2 : 1; }
 
 // ST: precision of the staged harmonics and radial factors (OutT, or double
 // for float64 arithmetic with float32 outputs), and of the coefficient scratch.
 template <typename PosT, typename OutT, int MODE, int RBF, bool HI, typename ST = OutT>
-__global__ __launch_bounds__(BSD, dens_min_waves(MODE, RBF, HI)) void k_density(Params P, Rows R, const PosT *__restrict__ pos, int W,
+__global__ __launch_bounds__(BSD, dens_min_waves(MODE, HI)) void k_density(Params P, Rows R, const PosT *__restrict__ pos, int W,
                                                  unsigned long long *__restrict__ work, WorkBase base,
                                                  OutT *__restrict__ desc,
                                                  OutT *__restrict__ c_out, OutT *__restrict__ jself,
@@ -1152,6 +1042,7 @@ __global__ __launch_bounds__(BSD, dens_min_waves(MODE, RBF, HI)) void k_density(
     for (int k = tid; k < n; k += BSD) c0[k] = P.c0[k];
     // structure index of the batch's first edge: edge outputs are batch-local
     const int64_t ebase = CCJ ? *R.e_origin : 0;
+    const int64_t rad0 = RBF == RBF_BUFFERED ? *P.rad_origin : 0;
 
     // the next center: its rows are loaded before the current center's
     // outputs are stored, so those loads never wait behind the stores
@@ -1250,7 +1141,7 @@ __global__ __launch_bounds__(BSD, dens_min_waves(MODE, RBF, HI)) void k_density(
             for (int off = wave * W; off < rbn; off += NWD * W) {
                 const int nb = (rbn - off) < W ? (rbn - off) : W;
                 const double *geo = rgeo + 4 * off;
-                stage_edges<JAC, ST, 0, 0, ST, RBF>(P, T, YY, yl, BB, X, geo, nb, lane, lg0, lg1, false, rb0 + off);
+                stage_edges<JAC, ST, 0, 0, ST, RBF>(P, T, YY, yl, BB, X, geo, nb, lane, lg0, lg1, rb0 + off - rad0);
                 for (int e = 0; e < nb; ++e) {
                     const int s = __builtin_amdgcn_readfirstlane(rsp[off + e]);
                     if (s != cur) {
@@ -1716,13 +1607,39 @@ __global__ __launch_bounds__(BSC) void k_desc(Params P, Rows R, const PosT *__re
 // coefficients, transposed to [lm][species n], for k_jacobian.  Each sum runs
 // in row order: deterministic with no ordering protocol.
 // ---------------------------------------------------------------------------
-// LDS doubles of k_djac: tables (K_l, Nt, a', betaC, c0), then the
+// The radial factors of a chunk's nb edges (e0: the first, from
+// *P.rad_origin) to the staging rows Bl, Hl [l][n][W + 1]: all threads in the
+// edges' order, four loads in flight per thread.
+template <typename ST>
+__device__ __forceinline__ void stage_radial(const Params &P, int64_t e0, int nb, int tid, ST *__restrict__ Bl,
+                                             ST *__restrict__ Hl, int ldl, int WP) {
+    const int lw = P.lmax + 1, per = P.n * lw, cnt = nb * per;
+    const float inv_per = 1.0f / (float)per, inv_lw = 1.0f / (float)lw;
+    for (int k0 = tid; k0 < cnt; k0 += 4 * BSC) {
+        typename Pair<ST>::type v[4];
+        int o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + u * BSC < cnt ? k0 + u * BSC : k0;
+            const int e = qdiv(k, inv_per), t = k - e * per, a = qdiv(t, inv_lw), l = t - a * lw;
+            v[u] = load_pair<ST>(rad_row<ST>(P, e0 + e), t);
+            o[u] = l * ldl + a * WP + e;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { // past the end: the first entry again
+            Bl[o[u]] = v[u].x;
+            Hl[o[u]] = v[u].y;
+        }
+    }
+}
+
+// LDS doubles of k_djac: tables (K_l, Nt, c0; GTO: a', betaC, the exponential's), then the
 // larger of the staging buffers (harmonics [lm][W+1], B and Bh [l][n][W+1]
 // with odd row lengths, edge vectors [W][4], species [W], species run bounds)
 // and the coefficient block 4 S n L
 __host__ __device__ __forceinline__ size_t djac_table_doubles(const Params &P) {
     const size_t ldN = (size_t)P.lmax + 2, lw = (size_t)P.lmax + 1, n = (size_t)P.n;
-    return 16 + even(ldN * ldN) + even(lw * n) + even(lw * n * n) + even(n) + 128;
+    return 16 + even(ldN * ldN) + even(n) + (P.rbf == 0 ? even(lw * n) + even(lw * n * n) + 128 : 0);
 }
 __host__ __device__ __forceinline__ size_t djac_stage_doubles(const Params &P, int W, int sb) {
     const size_t L = (size_t)P.L, lw = (size_t)P.lmax + 1, n = (size_t)P.n;
@@ -1735,7 +1652,7 @@ __host__ __device__ __forceinline__ size_t djac_lds_doubles(const Params &P, int
     return djac_table_doubles(P) + djac_stage_doubles(P, W, sb);
 }
 
-template <typename PosT, typename OutT, typename ST, int QT, int NA, int SR>
+template <typename PosT, typename OutT, typename ST, int QT, int SR, int RBF, int NA>
 __global__ __launch_bounds__(BSC) void k_djac(Params P, Rows R, const PosT *__restrict__ pos, int W,
                                               OutT *__restrict__ desc, OutT *__restrict__ jself,
                                               ST *__restrict__ c_scratch) {
@@ -1748,10 +1665,13 @@ __global__ __launch_bounds__(BSC) void k_djac(Params P, Rows R, const PosT *__re
     Carver cv{smem};
     double *Kl = cv.take(16);
     double *Nt = cv.take((size_t)ldN * ldN);
-    double *apr = cv.take((size_t)lw * n);
-    double *bcf = cv.take((size_t)lw * n * n);
     double *c0 = cv.take((size_t)n);
-    double *e2 = cv.take(128); // 2^(j/64) pairs of exp_neg_tab
+    double *apr = nullptr, *bcf = nullptr, *e2 = nullptr;
+    if constexpr (RBF == 0) {
+        apr = cv.take((size_t)lw * n);
+        bcf = cv.take((size_t)lw * n * n);
+        e2 = cv.take(128); // 2^(j/64) pairs of exp_neg_tab
+    }
     double *stage = cv.take(0);
     const int WP = W + 1, ldl = desc_ldl(n, W);
     Carver sv{stage};
@@ -1764,10 +1684,12 @@ __global__ __launch_bounds__(BSC) void k_djac(Params P, Rows R, const PosT *__re
     double *cb = stage;                                      // [c, Dx, Dy, Dz][S][n][L], after the row
     if (tid < 16) Kl[tid] = M_PI * sqrt(8.0 / (double)(2 * tid + 1));
     for (int k = tid; k < ldN * ldN; k += BSC) Nt[k] = P.Nt[k];
-    for (int k = tid; k < lw * n; k += BSC) apr[k] = P.aprime[k];
-    for (int k = tid; k < lw * n * n; k += BSC) bcf[k] = P.betaC[k];
     for (int k = tid; k < n; k += BSC) c0[k] = P.c0[k];
-    for (int k = tid; k < 128; k += BSC) e2[k] = P.e2t[k];
+    if constexpr (RBF == 0) {
+        for (int k = tid; k < lw * n; k += BSC) apr[k] = P.aprime[k];
+        for (int k = tid; k < lw * n * n; k += BSC) bcf[k] = P.betaC[k];
+        for (int k = tid; k < 128; k += BSC) e2[k] = P.e2t[k];
+    }
 
     // this thread's tasks: (lm, radial pair) = (t % L, t / L), t = tid + BSC q,
     // and the gradient of its S_lm: gx = g0 Y'_0 + g1 Y'_1, gy = g2 Y'_2 + g3 Y'_3,
@@ -1812,6 +1734,7 @@ __global__ __launch_bounds__(BSC) void k_djac(Params P, Rows R, const PosT *__re
             gc[q][j] = in ? c[j] : 0.0;
         }
     }
+    const int64_t rad0 = RBF == RBF_BUFFERED ? *P.rad_origin : 0;
     int64_t ci = blockIdx.x;
     const int64_t stride = gridDim.x;
     double gx = 0.0, gy = 0.0, gz = 0.0;
@@ -1868,37 +1791,42 @@ __global__ __launch_bounds__(BSC) void k_djac(Params P, Rows R, const PosT *__re
                     if (lane == 0) run[sr] = cnt;
                 }
             }
-            if (lane < nb) {
-                const double r2 = gx * gx + gy * gy + gz * gz;
-                for (int task = wave; task <= lw; task += NWC) {
-                    if (task == lw) {
-                        sh_all_any(gx, gy, gz, Nt, ldN, lw, Yl + lane, WP);
-                        continue;
-                    }
-                    const int l = task;
-                    // e_k and -2 a'_k e_k: Bh = sum_k betaC (-2 a'_k) e_k
-                    double ex[NA], ea[NA];
-#pragma unroll
-                    for (int k = 0; k < NA; ++k) {
-                        const double ap = apr[l * n + (k < n ? k : n - 1)];
-                        const double v = exp_neg_tab(ap * r2, e2);
-                        ex[k] = k < n ? v : 0.0;
-                        ea[k] = -2.0 * ap * ex[k];
-                    }
-                    ST *bo = Bl + (size_t)l * ldl + lane, *ho = Hl + (size_t)l * ldl + lane;
-                    const double *bc = bcf + (size_t)l * n * n;
-                    for (int a = 0; a < n; ++a) {
-                        double b = 0.0, h = 0.0;
-#pragma unroll
-                        for (int k = 0; k < NA; ++k) {
-                            const double cf = bc[a * n + (k < n ? k : n - 1)];
-                            b += cf * ex[k];
-                            h += cf * ea[k];
+            if constexpr (RBF == 0) {
+                if (lane < nb) {
+                    const double r2 = gx * gx + gy * gy + gz * gz;
+                    for (int task = wave; task <= lw; task += NWC) {
+                        if (task == lw) {
+                            sh_all_any(gx, gy, gz, Nt, ldN, lw, Yl + lane, WP);
+                            continue;
                         }
-                        bo[a * WP] = (ST)b;
-                        ho[a * WP] = (ST)h;
+                        const int l = task;
+                        // e_k and -2 a'_k e_k: Bh = sum_k betaC (-2 a'_k) e_k
+                        double ex[NA], ea[NA];
+    #pragma unroll
+                        for (int k = 0; k < NA; ++k) {
+                            const double ap = apr[l * n + (k < n ? k : n - 1)];
+                            const double v = exp_neg_tab(ap * r2, e2);
+                            ex[k] = k < n ? v : 0.0;
+                            ea[k] = -2.0 * ap * ex[k];
+                        }
+                        ST *bo = Bl + (size_t)l * ldl + lane, *ho = Hl + (size_t)l * ldl + lane;
+                        const double *bc = bcf + (size_t)l * n * n;
+                        for (int a = 0; a < n; ++a) {
+                            double b = 0.0, h = 0.0;
+    #pragma unroll
+                            for (int k = 0; k < NA; ++k) {
+                                const double cf = bc[a * n + (k < n ? k : n - 1)];
+                                b += cf * ex[k];
+                                h += cf * ea[k];
+                            }
+                            bo[a * WP] = (ST)b;
+                            ho[a * WP] = (ST)h;
+                        }
                     }
                 }
+            } else {
+                stage_radial<ST>(P, cs - rad0, nb, tid, Bl, Hl, ldl, WP);
+                if (wave == NWC - 1 && lane < nb) sh_all_any(gx, gy, gz, Nt, ldN, lw, Yl + lane, WP);
             }
             lds_barrier();
             // ---- projection, thread = (lm, radial pair), species run by run ----
@@ -2038,12 +1966,11 @@ __device__ __forceinline__ void sh_cols_lane(double x, double y, double z, const
     }
 }
 
-// LDS doubles of k_djs: tables (Nt, on-site terms; GTO: a', betaC), then the
-// staging (harmonics [lm][W+1], B and Bh [l][n][W+1] with odd row lengths,
+// LDS doubles of k_djs: tables (Nt, on-site terms), then the staging (harmonics [lm][W+1], B and Bh [l][n][W+1] with odd row lengths,
 // edge vectors [W][4], species [W], species run bounds)
 __host__ __device__ __forceinline__ size_t djs_lds_doubles(const Params &P, int W, int sb) {
     const size_t ldN = (size_t)P.lmax + 2, lw = (size_t)P.lmax + 1, n = (size_t)P.n, L = (size_t)P.L;
-    const size_t tables = even(ldN * ldN) + even(n) + (P.rbf == 0 ? even(lw * n) + even(lw * n * n) : 0);
+    const size_t tables = even(ldN * ldN) + even(n);
     return tables + even((L * (W + 1) * sb + 7) / 8) + 2 * even((lw * desc_ldl((int)n, W) * sb + 7) / 8) +
            4 * (size_t)W + even(((size_t)W + 1) / 2) + 16;
 }
@@ -2052,7 +1979,7 @@ __host__ __device__ __forceinline__ int djs_tasks(const Params &P) {
     return (P.L * ((P.n + 1) / 2) + BSC - 1) / BSC;
 }
 
-template <typename PosT, typename ST, int QT, int NA, int RBF>
+template <typename PosT, typename ST, int QT>
 __global__ __launch_bounds__(BSC) void k_djs(Params P, Rows R, const PosT *__restrict__ pos, int W,
                                              ST *__restrict__ c_scratch) {
     extern __shared__ __align__(16) double smem[];
@@ -2064,8 +1991,6 @@ __global__ __launch_bounds__(BSC) void k_djs(Params P, Rows R, const PosT *__res
     Carver cv{smem};
     double *Nt = cv.take((size_t)ldN * ldN);
     double *c0 = cv.take((size_t)n);
-    double *apr = RBF == 0 ? cv.take((size_t)lw * n) : nullptr;
-    double *bcf = RBF == 0 ? cv.take((size_t)lw * n * n) : nullptr;
     const int WP = W + 1, ldl = desc_ldl(n, W);
     ST *Yl = (ST *)cv.take(((size_t)L * WP * SB + 7) / 8);  // [lm][W + 1]
     ST *Bl = (ST *)cv.take(((size_t)lw * ldl * SB + 7) / 8); // [l][n][W + 1]
@@ -2074,10 +1999,6 @@ __global__ __launch_bounds__(BSC) void k_djs(Params P, Rows R, const PosT *__res
     int *run = (int *)cv.take(16);                           // species run bounds of the chunk
     for (int k = tid; k < ldN * ldN; k += BSC) Nt[k] = P.Nt[k];
     for (int k = tid; k < n; k += BSC) c0[k] = P.c0[k];
-    if constexpr (RBF == 0) {
-        for (int k = tid; k < lw * n; k += BSC) apr[k] = P.aprime[k];
-        for (int k = tid; k < lw * n * n; k += BSC) bcf[k] = P.betaC[k];
-    }
     lds_barrier(); // the tables (a center without neighbours reads the on-site terms before any chunk)
 
     // this thread's tasks: (radial pair, lm) = (t % np, t / np), t = tid + BSC q,
@@ -2121,8 +2042,7 @@ __global__ __launch_bounds__(BSC) void k_djs(Params P, Rows R, const PosT *__res
             gc[q][j] = in ? c[j] : 0.0;
         }
     }
-    const int per = n * lw;
-    const float inv_per = 1.0f / (float)per, inv_lw = 1.0f / (float)lw;
+    const int64_t rad0 = *P.rad_origin;
     int64_t ci = blockIdx.x;
     const int64_t stride = gridDim.x;
     double gx = 0.0, gy = 0.0, gz = 0.0;
@@ -2196,45 +2116,8 @@ __global__ __launch_bounds__(BSC) void k_djs(Params P, Rows R, const PosT *__res
                     if (lane == 0) run[s] = cnt;
                 }
             }
-            if constexpr (RBF == 1) {
-                // the chunk's radial factors, [edge][n][l] in the buffer, contiguous over the chunk
-                const double2 *rad = P.rad + (cs - P.rad_e0) * (size_t)per;
-                for (int k = tid; k < nb * per; k += BSC) {
-                    const int e = qdiv(k, inv_per), t = k - e * per, a = qdiv(t, inv_lw), l = t - a * lw;
-                    const double2 v = rad[k];
-                    Bl[l * ldl + a * WP + e] = (ST)v.x;
-                    Hl[l * ldl + a * WP + e] = (ST)v.y;
-                }
-            }
-            if (lane < nb) {
-                if constexpr (RBF == 0) {
-                    const double r2 = gx * gx + gy * gy + gz * gz;
-                    for (int l = wave; l < lw; l += NWC) {
-                        // e_k and -2 a'_k e_k: Bh = sum_k betaC (-2 a'_k) e_k
-                        double ex[NA], ea[NA];
-#pragma unroll
-                        for (int k = 0; k < NA; ++k) {
-                            const double ap = apr[l * n + (k < n ? k : n - 1)];
-                            ex[k] = k < n ? exp(-ap * r2) : 0.0;
-                            ea[k] = -2.0 * ap * ex[k];
-                        }
-                        ST *bo = Bl + (size_t)l * ldl + lane, *ho = Hl + (size_t)l * ldl + lane;
-                        const double *bc = bcf + (size_t)l * n * n;
-                        for (int a = 0; a < n; ++a) {
-                            double b = 0.0, h = 0.0;
-#pragma unroll
-                            for (int k = 0; k < NA; ++k) {
-                                const double cf = bc[a * n + (k < n ? k : n - 1)];
-                                b += cf * ex[k];
-                                h += cf * ea[k];
-                            }
-                            bo[a * WP] = (ST)b;
-                            ho[a * WP] = (ST)h;
-                        }
-                    }
-                }
-                sh_cols_lane(gx, gy, gz, Nt, ldN, lw, Yl + lane, WP, wave, NWC);
-            }
+            stage_radial<ST>(P, cs - rad0, nb, tid, Bl, Hl, ldl, WP);
+            if (lane < nb) sh_cols_lane(gx, gy, gz, Nt, ldN, lw, Yl + lane, WP, wave, NWC);
             lds_barrier();
             // ---- projection, thread = (radial pair, lm), species run by run ----
             for (int s = 0; s < S; ++s) {
@@ -2595,10 +2478,10 @@ constexpr int jac_min_waves(int ab, int NT, int LWT) {
     return (ab == 4 && (LWT == 0 || LWT <= 5 || (LWT == 7 && NT <= 8))) ? 3 : 2;
 }
 
-// RBF: -1 reads the radial basis from P (0..2); 3 is the compensated GTO
 // AT: precision of the final assembly (OutT, or double for float64
 // arithmetic with float32 outputs).
-template <typename PosT, typename OutT, int NT, int LWT, int RBF = -1, typename AT = OutT>
+// RBF: 0 the GTO factors evaluated in the staging, else the radial pass's
+template <typename PosT, typename OutT, int NT, int LWT, int RBF, typename AT = OutT>
 __global__ __launch_bounds__(BSJ, jac_min_waves(sizeof(AT), NT, LWT)) void k_jacobian(Params P, Rows R, const PosT *__restrict__ pos,
                                                                             int W, int vec, const AT *__restrict__ c_scratch,
                                                                             OutT *__restrict__ jedge) {
@@ -2626,10 +2509,10 @@ __global__ __launch_bounds__(BSJ, jac_min_waves(sizeof(AT), NT, LWT)) void k_jac
     // this wave's private staging
     Carver wv{cv.take(0) + (size_t)wave * jac_wave_doubles(P, W, ab)};
     double *YY = wv.take((size_t)W * 4 * L); // [e][S, dS/dx, dS/dy, dS/dz][L]
-    AT2 *BB = (AT2 *)wv.take(2 * (size_t)W * nl * ab / 8); // [e][n][l] = K_l (B, Bh)
+    AT2 *BB = (AT2 *)wv.take(2 * (size_t)W * nl * ab / 8); // [e][n][l] = (B, Bh)
     double *XU = wv.take((size_t)W * jac_xu_doubles(P, ab));
     // precontraction results, aliasing the radial scratch: U2a[e][u][l] =
-    // (U, Vx), U2b[e][u][l] = (Vy, Vz)
+    // K_l (U, Vx), U2b[e][u][l] = K_l (Vy, Vz)
     AT2 *U2a = (AT2 *)XU, *U2b = U2a + (size_t)W * Sn * lw;
 
     for (int k = tid; k < tri_lw; k += BSJ) dtab[k] = P.dtab[k];
@@ -2657,6 +2540,7 @@ __global__ __launch_bounds__(BSJ, jac_min_waves(sizeof(AT), NT, LWT)) void k_jac
     {
     const int64_t ci = blockIdx.x;
     const int64_t e0 = R.row_ptr[ci], e1 = R.row_ptr[ci + 1], ebase = *R.e_origin;
+    const int64_t rad0 = RBF == RBF_BUFFERED ? *P.rad_origin : 0;
     if (e1 == e0) return;
     const AT *cg = c_scratch + ci * 4 * (size_t)Sn * L; // component c of [c, Dx, Dy, Dz]
     copy_to_lds<BSJ, 4>(cT, cg, Sn * L, tid);
@@ -2682,7 +2566,7 @@ __global__ __launch_bounds__(BSJ, jac_min_waves(sizeof(AT), NT, LWT)) void k_jac
             const double *geo = rgeo + 4 * off;
             const int *spc = rsp + off;
             stage_edges<true, AT, NT, LWT, double, RBF>(P, T, YY, YLayout{4 * L, L, 1, 0}, BB, XU, geo, nb, lane, 0, lw,
-                                                        true, rb0 + off);
+                                                        rb0 + off - rad0);
 
             // ---- precontraction on the matrix cores ----
             // chunks j = (l, ch) in l-major order, operands loaded JB at a time
@@ -2718,8 +2602,9 @@ __global__ __launch_bounds__(BSJ, jac_min_waves(sizeof(AT), NT, LWT)) void k_jac
                                 if (++ch == (l >> 1) + 1) {
                                     if (o_e < nb && uok) {
                                         const size_t qq = (size_t)(o_e * Sn + u) * lw + l;
-                                        U2a[qq] = Pair<AT>::make(acc[0], acc[1]);
-                                        U2b[qq] = Pair<AT>::make(acc[2], acc[3]);
+                                        const double K = T.Kl[l];
+                                        U2a[qq] = Pair<AT>::make(K * acc[0], K * acc[1]);
+                                        U2b[qq] = Pair<AT>::make(K * acc[2], K * acc[3]);
                                     }
                                     acc = dbl4{0.0, 0.0, 0.0, 0.0};
                                     ch = 0;

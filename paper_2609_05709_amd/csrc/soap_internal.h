@@ -11,11 +11,13 @@ constexpr int LMAX = 14;       // largest l_max
 constexpr int LT_MAX = LMAX + 2;
 constexpr int MAX_GROUPS = LMAX + 1;
 constexpr int MAX_DEGREE = 2048;
+constexpr int RBF_BUFFERED = 1; // the polynomial quadrature always reads the buffer
 
 // Everything the descriptor kernels need about the basis; passed by value.
 struct Params {
     int S, n, lmax, L, rbf, Q; // L = (lmax+1)^2; rbf 0 GTO, 1 polynomial, 2 polynomial (Laplace form),
-                               // 3 GTO with the compensated float64 evaluation
+                               // 3 GTO with the compensated float64 evaluation; kernels that read the
+                               // radial pass's buffer are planned and launched with RBF_BUFFERED
     int F, Fe, nq_full;        // features, edge features, (mu,nu,n,n') combinations
     double sigma, inv_s2;      // 1 / sigma^2
     double rc, inv_rc2;        // cutoff radius, 2 / rc
@@ -27,13 +29,20 @@ struct Params {
     const double *G;           // polynomial [n][Q], includes 4 pi
     const double *rq;          // polynomial [Q]
     const double *WN;          // polynomial, Laplace form [n][n+3][4]: Chebyshev series of P_n0..P_n3 on [0, rc]
-    const double2 *rad;        // polynomial quadrature: radial factors (B_nl, Bh_nl) of the call's edges,
-                               // [edge - rad_e0][n][l] (k_radial)
-    int64_t rad_e0;            // structure index of the first edge of rad
+    const void *rad;           // radial factors of a range's edges (the radial pass): edge e has its pairs
+                               // (B_nl, Bh_nl), [n][l] at the staging precision, at byte (e - *rad_origin) *
+                               // rad_stride (4-byte aligned: they may lie in the edge's Jacobian block)
+    int64_t rad_stride;        // bytes per edge
+    const int64_t *rad_origin; // row offset of the range's first center
+    const void *rtab;          // table of the radial factors (radial.hip; NULL: none), records [interval][n][l]
+    int rtab_k;                // intervals on [0, r_cut]
+    double rtab_inv_h;         // intervals per length
     const double *c0;          // on-site term [n]
     const double *e2t;         // GTO: [64][2] 2^(j/64) as (value, remainder) (soap_exp2_table64)
     const double *Nt;          // [lmax+2][lmax+2] N_lm (2m-1)!! / (l-m)! (division-free recurrence)
     const double *gcoef;       // [(l, m >= 0)][4] gradient identities of the harmonics (cA, cB, cC, l | m << 8)
+    const double *jab;         // rows of the edge Jacobian's products (jacobian_blocks.hip): alpha [4][L + 3], beta [2][L + 3]
+    const uint16_t *jpq;       // and p | q << 8 [4][L + 3]
     const uint32_t *dtab;      // [tri_lw] diagonal-pair slots: (n lw + l) | (n' lw + l) << 16, n' >= n
     int tri_lw;                // n (n + 1) / 2 * (l_max + 1)
     int n_groups;              // l-groups of the density kernel
@@ -146,7 +155,7 @@ struct DensityLaunch {
     int W;           // edges per wave iteration
     size_t lds;      // dynamic LDS bytes
     int blocks;      // persistent workgroups per l-group
-    bool hi;         // the variant compiled for three waves per SIMD (see density_has_high)
+    bool hi;         // the variant compiled for two waves per SIMD (mode 2)
 };
 struct DescLaunch {
     int W;          // edges per chunk (0: the descriptor path uses k_density)
@@ -156,13 +165,13 @@ struct DescLaunch {
 };
 struct DjacLaunch {
     int W;          // edges per chunk (0: the Jacobian path uses k_density)
-    int qt, na, sr; // tasks per thread, radial size, species slots
+    int qt, na, sr; // tasks per thread, radial size (GTO), species slots
     size_t lds;
     int blocks;     // resident workgroups (persistent launch)
 };
 struct DjsLaunch {
     int W;          // edges per chunk (0: not used)
-    int qt, na;     // tasks per thread, radial size (GTO)
+    int qt;         // tasks per thread
     size_t lds;
     int blocks;     // resident workgroups (persistent launch)
 };
@@ -175,12 +184,12 @@ struct JacLaunch {
 size_t density_lds_bytes(const Params &P, int jac, int lg0, int lg1, int W, bool st64);
 // f64: float64 positions and outputs; ar64: float64 arithmetic with float32 outputs
 int density_blocks_per_cu(bool f64, bool ar64, int mode, int rbf, bool hi, size_t lds); // mode as launch_density
-bool density_has_high(int mode, int rbf); // a three-waves-per-SIMD variant exists
 constexpr int DENSITY_KE = 8; // coefficient entries per lane in k_density: n * Lg <= 512
 size_t jacobian_lds_bytes(const Params &P, int W, bool at64); // at64: float64 assembly
 int jacobian_max_w();
 // resident workgroups per CU (0 if it does not fit)
 int jacobian_blocks_per_cu(bool f64, bool ar64, int rbf, int n, int lw, size_t lds);
+bool jacobian_has_fixed(int n, int lw); // a float32 GTO kernel compiled for this basis size
 // float32 Jacobian kernels for fixed (n_max, l_max + 1); NULL if not compiled
 const void *jacobian_fixed_0(int n, int lw);
 const void *jacobian_fixed_1(int n, int lw);
@@ -220,27 +229,46 @@ size_t desc_lds_bytes(const Params &P, int W, bool st64);
 int desc_blocks_per_cu(bool f64, bool ar64, int ql, int na, int sr, size_t lds);
 hipError_t launch_desc(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64, const DescLaunch &cfg,
                        void *desc, void *c_out, hipStream_t st);
-// one-workgroup-per-center density step of the Jacobian path (GTO): shape,
-// LDS bytes, resident workgroups per CU, launch (writes desc, jself and the
+// one-workgroup-per-center density step of the Jacobian path: shape, LDS
+// bytes, resident workgroups per CU, launch (writes desc, jself and the
 // coefficients for k_jacobian)
 bool djac_shape(const Params &P, int *qt, int *na, int *sr);
 size_t djac_lds_bytes(const Params &P, int W, bool st64);
-// the polynomial quadrature's radial pass: (B_nl, Bh_nl) of every edge of the
-// rows, at out[edge - e_base][n][l]
-size_t radial_bytes_per_edge(const Params &P);
-hipError_t launch_radial(const Params &P, const Rows &R, const void *pos, bool f64, int64_t e_base, void *out,
+// the radial pass (radial.hip): (B_nl, Bh_nl) of every edge of the rows to
+// P.rad; st64: pairs of float64
+size_t radial_bytes_per_edge(const Params &P, bool st64);
+// degree: edges per center, about (shapes the launch)
+hipError_t launch_radial(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64, double degree,
                          hipStream_t st);
-int djac_blocks_per_cu(bool f64, bool ar64, int qt, int na, int sr, size_t lds);
+// the table of the radial factors (0 intervals: the basis has none)
+int radial_table_intervals(const Params &P, bool st64);
+size_t radial_table_bytes(const Params &P, bool st64);
+hipError_t build_radial_table(const Params &P, bool st64, void *tab);
+hipError_t radial_set_lds_limit(int lim);
+int djac_blocks_per_cu(bool f64, bool ar64, int rbf, int qt, int na, int sr, size_t lds);
 hipError_t launch_djac(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64, const DjacLaunch &cfg,
                        void *desc, void *jself, void *c_scratch, hipStream_t st);
 hipError_t launch_jacobian(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64, const JacLaunch &cfg,
                            const void *c_scratch, void *jedge, hipStream_t st);
+// the edge Jacobian kernel (jacobian_blocks.hip): plan (false if the basis has
+// none: more than 64 coefficients per (l, m), or on-chip memory) and launch
+struct EdgeBlocksLaunch {
+    int Q;       // quads of edges per chunk (0: not used)
+    int RB;      // edges per row block
+    int split;   // workgroups per center
+    int threads;
+    size_t lds;
+};
+bool eb_plan(const Params &P, bool f64, bool ar64, EdgeBlocksLaunch *out);
+hipError_t launch_edge_blocks(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64,
+                              const EdgeBlocksLaunch &cfg, const void *c_scratch, void *jedge, hipStream_t st);
+hipError_t eb_set_lds_limit(int lim);
 // density step of the Jacobian path with the coefficients streamed to the
-// scratch (k_djs, density_streamed.hip): GTO and polynomial quadrature bases
-// of at most four (radial pair, lm) tasks per thread
-bool djs_shape(const Params &P, int *qt, int *na);
+// scratch (k_djs, density_streamed.hip): bases of at most four (radial pair,
+// lm) tasks per thread
+bool djs_shape(const Params &P, int *qt);
 size_t djs_lds_bytes(const Params &P, int W, bool st64);
-int djs_blocks_per_cu(bool f64, bool ar64, int rbf, int qt, int na, size_t lds);
+int djs_blocks_per_cu(bool f64, bool ar64, int qt, size_t lds);
 hipError_t launch_djs(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64, const DjsLaunch &cfg,
                       void *c_scratch, hipStream_t st);
 hipError_t djs_set_lds_limit(int lim);

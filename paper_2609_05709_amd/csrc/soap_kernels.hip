@@ -16,24 +16,25 @@ size_t density_lds_bytes(const Params &P, int jac, int lg0, int lg1, int W, bool
 
 // the density kernel of a precision (positions and outputs T, staging ST),
 // mode, radial basis and occupancy variant
-template <typename T, typename ST, int RBF, bool HI>
-static const void *density_kernel_r(int mode) {
-    return mode == 0 ? (const void *)dev::k_density<T, T, 0, RBF, false, ST>
-                     : mode == 1 ? (const void *)dev::k_density<T, T, 1, RBF, HI && dev::dens_has_high(1, RBF), ST>
-                                 : (const void *)dev::k_density<T, T, 2, RBF, HI, ST>;
-}
+// (mode 1 reads the radial pass's factors for every basis)
 template <typename T, typename ST, int RBF>
-static const void *density_kernel_h(int mode, bool hi) {
-    return hi ? density_kernel_r<T, ST, RBF, true>(mode) : density_kernel_r<T, ST, RBF, false>(mode);
+static const void *density_kernel_r(int mode, bool hi) {
+    if (mode == 0) return (const void *)dev::k_density<T, T, 0, RBF, false, ST>;
+    if (mode == 1) {
+        if constexpr (RBF == RBF_BUFFERED) return (const void *)dev::k_density<T, T, 1, RBF, false, ST>;
+        return nullptr;
+    }
+    return hi ? (const void *)dev::k_density<T, T, 2, RBF, true, ST>
+              : (const void *)dev::k_density<T, T, 2, RBF, false, ST>;
 }
 template <typename T, typename ST>
 static const void *density_kernel_t(int mode, int rbf, bool hi) {
     if (rbf == 3) { // the compensated GTO exists for float64 only
-        if constexpr (sizeof(T) == 8) return density_kernel_h<T, ST, 3>(mode, hi);
+        if constexpr (sizeof(T) == 8) return density_kernel_r<T, ST, 3>(mode, hi);
         return nullptr;
     }
-    return rbf == 0 ? density_kernel_h<T, ST, 0>(mode, hi)
-                    : (rbf == 1 ? density_kernel_h<T, ST, 1>(mode, hi) : density_kernel_h<T, ST, 2>(mode, hi));
+    return rbf == 0 ? density_kernel_r<T, ST, 0>(mode, hi)
+                    : (rbf == 1 ? density_kernel_r<T, ST, 1>(mode, hi) : density_kernel_r<T, ST, 2>(mode, hi));
 }
 // ar64: float64 staging with float32 outputs (ignored for float64 outputs)
 static const void *density_kernel(bool f64, bool ar64, int mode, int rbf, bool hi) {
@@ -63,59 +64,24 @@ static const void *desc_kernel(bool f64, bool ar64, int qt, int na, int sr) {
     return ar64 ? desc_kernel_t<float, double>(qt, na, sr) : desc_kernel_t<float, float>(qt, na, sr);
 }
 
-// k_djac variants: QT (lm, pair) tasks per thread, NA >= n_max, SR >= S species slots
+// k_djac variants: QT (lm, pair) tasks per thread, SR >= S species slots; GTO
+// with NA >= n_max exponentials per l, or the radial pass's factors
 template <typename T, typename ST, int SR>
-static const void *djac_kernel_s(int qt, int na) {
-    if (qt == 1 && na == 8) return (const void *)dev::k_djac<T, T, ST, 1, 8, SR>;
-    if (qt == 1 && na == 16) return (const void *)dev::k_djac<T, T, ST, 1, 16, SR>;
-    if (qt == 2 && na == 8) return (const void *)dev::k_djac<T, T, ST, 2, 8, SR>;
-    if (qt == 2 && na == 16) return (const void *)dev::k_djac<T, T, ST, 2, 16, SR>;
-    return nullptr;
+static const void *djac_kernel_s(int rbf, int qt, int na) {
+    if (rbf == RBF_BUFFERED)
+        return qt == 1 ? (const void *)dev::k_djac<T, T, ST, 1, SR, RBF_BUFFERED, 1>
+                       : (const void *)dev::k_djac<T, T, ST, 2, SR, RBF_BUFFERED, 1>;
+    if (qt == 1) return na == 8 ? (const void *)dev::k_djac<T, T, ST, 1, SR, 0, 8> : (const void *)dev::k_djac<T, T, ST, 1, SR, 0, 16>;
+    return na == 8 ? (const void *)dev::k_djac<T, T, ST, 2, SR, 0, 8> : (const void *)dev::k_djac<T, T, ST, 2, SR, 0, 16>;
 }
 template <typename T, typename ST>
-static const void *djac_kernel_t(int qt, int na, int sr) {
-    return sr == 2 ? djac_kernel_s<T, ST, 2>(qt, na) : (sr == 4 ? djac_kernel_s<T, ST, 4>(qt, na) : nullptr);
+static const void *djac_kernel_t(int rbf, int qt, int na, int sr) {
+    return sr == 2 ? djac_kernel_s<T, ST, 2>(rbf, qt, na) : djac_kernel_s<T, ST, 4>(rbf, qt, na);
 }
-static const void *djac_kernel(bool f64, bool ar64, int qt, int na, int sr) {
-    if (f64) return djac_kernel_t<double, double>(qt, na, sr);
-    return ar64 ? djac_kernel_t<float, double>(qt, na, sr) : djac_kernel_t<float, float>(qt, na, sr);
+static const void *djac_kernel(bool f64, bool ar64, int rbf, int qt, int na, int sr) {
+    if (f64) return djac_kernel_t<double, double>(rbf, qt, na, sr);
+    return ar64 ? djac_kernel_t<float, double>(rbf, qt, na, sr) : djac_kernel_t<float, float>(rbf, qt, na, sr);
 }
-
-// k_radial variants: NA >= n_max radial indices per lane
-template <typename T> static const void *radial_kernel_t(int na) {
-    if (na == 4) return (const void *)dev::k_radial<T, 4>;
-    if (na == 8) return (const void *)dev::k_radial<T, 8>;
-    if (na == 12) return (const void *)dev::k_radial<T, 12>;
-    if (na == 16) return (const void *)dev::k_radial<T, 16>;
-    return nullptr;
-}
-static const void *radial_kernel(bool f64, int na) { return f64 ? radial_kernel_t<double>(na) : radial_kernel_t<float>(na); }
-static int radial_na(int n) { return n <= 4 ? 4 : (n <= 8 ? 8 : (n <= 12 ? 12 : 16)); }
-
-size_t radial_bytes_per_edge(const Params &P) { return 16 * (size_t)P.n * (P.lmax + 1); }
-
-hipError_t launch_radial(const Params &P, const Rows &R, const void *pos, bool f64, int64_t e_base, void *out,
-                         hipStream_t st) {
-    if (R.nc <= 0) return hipSuccess;
-    const int na = radial_na(P.n);
-    const void *k = radial_kernel(f64, na);
-    const size_t lds = 8 * dev::radial_lds_doubles(P, na);
-    int ncu = 256, dev_id = 0, per = 0;
-    (void)hipGetDevice(&dev_id);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev_id);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, BSR, lds) != hipSuccess || per < 1) per = 1;
-    // blocks of cb centers: about 16 workgroups per CU of work, at most
-    // RAD_CB_MAX centers a block, the blocks striding over the centers
-    int cb = (int)std::min<int64_t>(RAD_CB_MAX, std::max<int64_t>(1, R.nc / (16 * (int64_t)ncu)));
-    const int64_t need = (R.nc + cb - 1) / cb;
-    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)ncu * per * 64));
-    Params Pk = P;
-    Rows Rk = R;
-    void *args[] = {&Pk, &Rk, &pos, &e_base, &cb, &out};
-    return hipLaunchKernel(k, dim3(blocks), dim3(BSR), args, lds, st);
-}
-
-bool density_has_high(int mode, int rbf) { return dev::dens_has_high(mode, rbf); }
 
 int density_blocks_per_cu(bool f64, bool ar64, int mode, int rbf, bool hi, size_t lds) {
     int nb = 0;
@@ -201,19 +167,25 @@ hipError_t launch_outputs(const Params &P, const OutPlan &O, int64_t nc, bool f6
 
 int jacobian_max_w() { return JAC_MAX_W; }
 
-// The float32 Jacobian kernel is also compiled for fixed (n_max, l_max + 1)
-// pairs (jacobian_fixed.hip); the generic kernel covers every other basis and
-// float64.
-const void *jacobian_kernel(bool f64, bool ar64, int rbf, int n, int lw) {
-    if (f64)
-        return rbf == 3 ? reinterpret_cast<const void *>(&k_jacobian<double, double, 0, 0, 3>)
-                        : reinterpret_cast<const void *>(&k_jacobian<double, double, 0, 0>);
-    if (rbf == 3) return nullptr; // float64 only
-    if (ar64) return reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, -1, double>);
+// rbf 0: the GTO factors evaluated in the kernel; RBF_BUFFERED: the radial
+// pass's.  The float32 GTO kernel is also compiled for fixed (n_max, l_max +
+// 1) pairs (jacobian_fixed.hip).
+static const void *jacobian_fixed(int n, int lw) {
     const void *k = jacobian_fixed_0(n, lw);
     if (!k) k = jacobian_fixed_1(n, lw);
-    if (!k) k = jacobian_fixed_2(n, lw);
-    return k ? k : reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0>);
+    return k ? k : jacobian_fixed_2(n, lw);
+}
+bool jacobian_has_fixed(int n, int lw) { return jacobian_fixed(n, lw) != nullptr; }
+const void *jacobian_kernel(bool f64, bool ar64, int rbf, int n, int lw) {
+    if (rbf != 0) {
+        if (f64) return reinterpret_cast<const void *>(&k_jacobian<double, double, 0, 0, RBF_BUFFERED>);
+        return ar64 ? reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, RBF_BUFFERED, double>)
+                    : reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, RBF_BUFFERED>);
+    }
+    if (f64) return reinterpret_cast<const void *>(&k_jacobian<double, double, 0, 0, 0>);
+    if (ar64) return reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, 0, double>);
+    const void *k = jacobian_fixed(n, lw);
+    return k ? k : reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, 0>);
 }
 
 int jacobian_blocks_per_cu(bool f64, bool ar64, int rbf, int n, int lw, size_t lds) {
@@ -231,7 +203,9 @@ hipError_t set_lds_limits() {
         for (int ar64 = 0; ar64 < 2; ++ar64)
             for (int mode = 0; mode < 3; ++mode)
                 for (int rbf = 0; rbf < (f64 ? 4 : 3); ++rbf)
-                    for (int hi = 0; hi < 2; ++hi) SOAP_SET(density_kernel(f64 != 0, ar64 != 0, mode, rbf, hi != 0));
+                    for (int hi = 0; hi < 2; ++hi)
+                        if (density_kernel(f64 != 0, ar64 != 0, mode, rbf, hi != 0))
+                            SOAP_SET(density_kernel(f64 != 0, ar64 != 0, mode, rbf, hi != 0));
     for (int f64 = 0; f64 < 2; ++f64)
         for (int ar64 = 0; ar64 < 2; ++ar64)
             for (int qt : {1, 2, 4})
@@ -242,10 +216,9 @@ hipError_t set_lds_limits() {
     for (int f64 = 0; f64 < 2; ++f64)
         for (int ar64 = 0; ar64 < 2; ++ar64)
             for (int qt : {1, 2})
-                for (int na : {8, 16})
-                    for (int sr : {2, 4}) SOAP_SET(djac_kernel(f64 != 0, ar64 != 0, qt, na, sr));
-    for (int f64 = 0; f64 < 2; ++f64)
-        for (int na : {4, 8, 12, 16}) SOAP_SET(radial_kernel(f64 != 0, na));
+                for (int sr : {2, 4})
+                    for (int na : {8, 16})
+                        for (int rbf : {0, RBF_BUFFERED}) SOAP_SET(djac_kernel(f64 != 0, ar64 != 0, rbf, qt, na, sr));
     SOAP_SET((k_outputs<float, float>));
     SOAP_SET((k_outputs<float, double>));
     SOAP_SET((k_outputs_rows<float, float>));
@@ -254,17 +227,15 @@ hipError_t set_lds_limits() {
     SOAP_SET((k_outputs<double, double>));
     SOAP_SET(k_power_single<float>);
     SOAP_SET(k_power_single<double>);
-    SOAP_SET((k_jacobian<float, float, 0, 0>));
-    SOAP_SET((k_jacobian<double, double, 0, 0>));
-    SOAP_SET((k_jacobian<double, double, 0, 0, 3>));
-    SOAP_SET((k_jacobian<float, float, 0, 0, -1, double>));
+    for (int v = 0; v < 3; ++v)
+        for (int rbf : {0, RBF_BUFFERED}) SOAP_SET(jacobian_kernel(v == 2, v == 1, rbf, NMAX, LMAX + 1));
     for (int n = 1; n <= NMAX; ++n)
-        for (int lw = 1; lw <= LMAX + 1; ++lw) {
-            const void *k = jacobian_kernel(false, false, 0, n, lw);
-            if (k != reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0>)) SOAP_SET(k);
-        }
+        for (int lw = 1; lw <= LMAX + 1; ++lw)
+            if (jacobian_has_fixed(n, lw)) SOAP_SET(jacobian_fixed(n, lw));
 #undef SOAP_SET
     if (e == hipSuccess) e = djs_set_lds_limit(lim);
+    if (e == hipSuccess) e = radial_set_lds_limit(lim);
+    if (e == hipSuccess) e = eb_set_lds_limit(lim);
     return e;
 }
 
@@ -321,21 +292,21 @@ hipError_t launch_desc(const Params &P, const Rows &R, const void *pos, bool f64
 }
 
 bool djac_shape(const Params &P, int *qt, int *na, int *sr) {
-    if (P.rbf != 0 || P.S > 4) return false;
+    if (P.S > 4) return false;
     const int t = (P.L * ((P.n + 1) / 2) + BSC - 1) / BSC;
     if (t > 2) return false;
     *qt = t <= 1 ? 1 : 2;
     *na = P.n <= 8 ? 8 : 16;
     *sr = P.S <= 2 ? 2 : 4;
-    return djac_kernel(false, false, *qt, *na, *sr) != nullptr;
+    return true;
 }
 
 size_t djac_lds_bytes(const Params &P, int W, bool st64) { return 8 * dev::djac_lds_doubles(P, W, st64 ? 8 : 4); }
 
-int djac_blocks_per_cu(bool f64, bool ar64, int qt, int na, int sr, size_t lds) {
+int djac_blocks_per_cu(bool f64, bool ar64, int rbf, int qt, int na, int sr, size_t lds) {
     int nb = 0;
     const hipError_t e =
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, djac_kernel(f64, ar64, qt, na, sr), BSC, lds);
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, djac_kernel(f64, ar64, rbf, qt, na, sr), BSC, lds);
     return (e == hipSuccess && nb > 0) ? nb : 0;
 }
 
@@ -347,7 +318,7 @@ hipError_t launch_djac(const Params &P, const Rows &R, const void *pos, bool f64
     int W = cfg.W;
     void *args[] = {&Pk, &Rk, &pos, &W, &desc, &jself, &c_scratch};
     const int64_t blocks = std::min<int64_t>(R.nc, (int64_t)cfg.blocks);
-    return hipLaunchKernel(djac_kernel(f64, ar64, cfg.qt, cfg.na, cfg.sr), dim3((unsigned)blocks), dim3(BSC), args,
+    return hipLaunchKernel(djac_kernel(f64, ar64, P.rbf, cfg.qt, cfg.na, cfg.sr), dim3((unsigned)blocks), dim3(BSC), args,
                            cfg.lds, st);
 }
 
