@@ -141,19 +141,21 @@ int soap_create(const int32_t *species_Z, int32_t n_species, double r_cut, int32
  *              whose waves each own whole centers, with at most that many
  *              edges per chunk (the widest that fits on chip);
  *   "jac_tile" : edges per matrix-core tile of the edge Jacobian kernel (a
- *              tuning knob, results identical up to rounding order): 0 =
- *              automatic (default: the most resident workgroups, then the
- *              widest tile), 1..4 = that width (a width whose LDS does not
- *              fit leaves the Jacobian path without a plan: the calls that
- *              need it return SOAP_EINVAL, as for a basis too large);
- *   "djac_tile": kernel choice of the density step of the GTO Jacobian path
+ *              tuning knob): 0 = automatic (default: by the basis, the kernel
+ *              that works on chunks of edges by whole workgroups, or the one
+ *              of wave tiles with the most resident workgroups, then the
+ *              widest tile), 1..4 = wave tiles of that width (results identical
+ *              up to rounding order; a width whose LDS does not fit leaves the
+ *              Jacobian path without a plan: the calls that need it return
+ *              SOAP_EINVAL, as for a basis too large);
+ *   "djac_tile": kernel choice of the density step of the Jacobian path
  *              (a tuning knob, results identical up to rounding order):
- *              0 = automatic (default), -1 = the shared density kernel and
- *              the output kernel, 32 / 64 = the kernel that gives each
+ *              0 = automatic (default), -1 = not the kernel that gives each
+ *              center a workgroup and writes its outputs, 32 / 64 = the kernel that gives each
  *              center a workgroup, with at most that many edges per chunk;
  *   "djs_tile" : kernel choice of the density step of the Jacobian path for
  *              the GTO bases outside "djac_tile"'s kernel and the polynomial
- *              quadrature bases (a tuning knob, results identical up to
+ *              bases (a tuning knob, results identical up to
  *              rounding order): 0 = automatic (default), -1 = the shared
  *              density kernel, 16 / 32 / 64 = the kernel that gives each
  *              center a workgroup and streams its coefficients to the
@@ -197,7 +199,11 @@ int soap_set_option(soap_ctx *ctx, const char *key, int64_t value);
  *                               kernel that gives each center a workgroup and
  *                               writes its outputs ("djac_tile"), 2 the one
  *                               that streams the coefficients to the scratch
- *                               ("djs_tile"), 0 the shared density kernel;
+ *                               ("djs_tile"), 3 the one that forms them on the
+ *                               matrix cores (larger bases, and a neighbour
+ *                               list of at least 8 edges per center and
+ *                               species on average, else 1, 2 or 0), 0 the
+ *                               shared density kernel;
  *   "output_kernel_rows"      : 1 if the output kernel of the Jacobian path
  *                               (run when the shared density kernel splits
  *                               l into groups, and after the streaming
@@ -209,8 +215,10 @@ int soap_set_option(soap_ctx *ctx, const char *key, int64_t value);
  *   "jacobian_density_tile", "jacobian_density_lds": edges per chunk and
  *                               LDS bytes per workgroup of the density step
  *                               of the Jacobian path;
- *   "jacobian_tile", "jacobian_lds": edges per wave tile and LDS bytes per
- *                               workgroup of the edge Jacobian kernel;
+ *   "jacobian_tile", "jacobian_lds": edges per wave tile (the kernel that
+ *                               works on chunks by whole workgroups: per
+ *                               chunk) and LDS bytes per workgroup of the edge
+ *                               Jacobian kernel;
  *   "output_lds"              : LDS bytes per workgroup of the output kernel.
  * Errors: SOAP_EINVAL (NULL argument, unknown key).
  */

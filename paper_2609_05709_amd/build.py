@@ -38,6 +38,8 @@ def _run(cmd):
 
 # the float32 Jacobian kernel for fixed basis sizes, in parts built in parallel
 FIXED_SOURCE, FIXED_PARTS = "jacobian_fixed.hip", 3
+# the density step of the Jacobian path, one part per precision
+MX_SOURCE, MX_PARTS = "density_matrix.hip", 3
 
 
 def build(verbose: bool = True) -> str:
@@ -51,6 +53,9 @@ def build(verbose: bool = True) -> str:
     for part in range(FIXED_PARTS):
         obj = os.path.join(BUILD, f"{FIXED_SOURCE}.{part}.o")
         jobs.append((obj, [HIPCC, *HIP_FLAGS, f"-DJF_PART={part}", "-c", os.path.join(CSRC, FIXED_SOURCE), "-o", obj]))
+    for part in range(MX_PARTS):
+        obj = os.path.join(BUILD, f"{MX_SOURCE}.{part}.o")
+        jobs.append((obj, [HIPCC, *HIP_FLAGS, f"-DDM_PART={part}", "-c", os.path.join(CSRC, MX_SOURCE), "-o", obj]))
     with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1)) as ex:
         list(ex.map(lambda j: _run(j[1]), jobs))
     objs = [j[0] for j in jobs]

@@ -134,6 +134,7 @@ struct soap_ctx {
     DescLaunch desc_cfg{};
     DjacLaunch djac_cfg{};
     int djac_tile = 0; // option "djac_tile": 0 auto (default), -1 never k_djac, else the widest chunk
+    DensityMxLaunch mx_cfg{}; // k_density_mx, in the place of k_djs and k_density (use_mx)
     DjsLaunch djs_cfg{};
     int djs_tile = 0; // option "djs_tile": 0 auto (default), -1 never k_djs, else the widest chunk
     // pipelined derivatives: the density kernel of center chunk k + 1 on the
@@ -415,6 +416,23 @@ int plan_launches(soap_ctx *c) {
             }
         }
     }
+    // k_density_mx, where k_djac has no plan or two tasks per thread, and no
+    // option asks for another kernel; one workgroup per CU where nothing else fits
+    c->mx_cfg = DensityMxLaunch{};
+    if (!c->inline_radial && (c->djac_cfg.W == 0 || c->djac_cfg.qt > 1) && c->djac_tile == 0 && c->djs_tile == 0 &&
+        c->out_ok) {
+        for (int least : {2, 1}) {
+            for (int W : {64, 32, 16}) {
+                const size_t lds = density_mx_lds(Pb, W, st64);
+                const int b = lds > LDS_HARD_LIMIT ? 0 : density_mx_blocks_per_cu(Pb, f64, ar64, lds);
+                if (b >= least) {
+                    c->mx_cfg = DensityMxLaunch{W, lds, ncu * b};
+                    break;
+                }
+            }
+            if (c->mx_cfg.W > 0 || c->djac_cfg.W > 0 || c->djs_cfg.W > 0) break;
+        }
+    }
     c->jac_ok = bestW > 0;
     // an explicit "jac_tile" asks for the kernel with that tile
     c->eb_cfg = EdgeBlocksLaunch{};
@@ -536,6 +554,48 @@ int upload_constants(soap_ctx *c) {
         }
     for (int d = 0; d < 4; ++d) // past the last harmonic: zero rows
         for (int k = Ll; k < Lp; ++k) jpq[(size_t)d * Lp + k] = (uint16_t)(Ll | Ll << 8);
+    // T- and T+ of the density step: D_lm = T- (sums over S_{l-1}) + T+ (sums over
+    // S_{l+1}), per lm the (x, y: two, z: one) coefficients of T-, then of T+,
+    // and their harmonics.  T- is the gradient; T+ that of the degree l + 1
+    // harmonics, transposed, over 2l + 3.
+    std::vector<double> dtm(10 * (size_t)Ll, 0.0);
+    std::vector<uint16_t> dti(6 * (size_t)Ll, 0);
+    for (int lm = 0; lm < Ll; ++lm)
+        for (int d = 0; d < 3; ++d) {
+            dtm[(size_t)(2 * d) * Ll + lm] = jab[(size_t)(d + 1) * Lp + lm];
+            if (d < 2) dtm[(size_t)(2 * d + 1) * Ll + lm] = jab[(size_t)(4 + d) * Lp + lm];
+            dti[(size_t)d * Ll + lm] = jpq[(size_t)(d + 1) * Lp + lm];
+        }
+    for (int l = 0; l <= c->lmax; ++l)
+        for (int k = -l; k <= l; ++k) {
+            const int lm = l * l + l + k, l1 = l + 1, kk = k < 0 ? -k : k;
+            // gradient coefficients of S_{l1,m} (cA, cB, cC as above)
+            auto N1 = [&](int m) { return (long double)Nlm[(size_t)l1 * ldN + m]; };
+            auto N0 = [&](int m) { return (long double)Nlm[(size_t)l * ldN + m]; };
+            auto cA = [&](int m) { return m + 1 <= l ? (m == 0 ? N1(m) : N1(m) / 2) / N0(m + 1) : 0.0L; };
+            auto cB = [&](int m) { return m >= 1 ? N1(m) * (long double)((l1 + m) * (l1 + m - 1)) / (2 * N0(m - 1)) : 0.0L; };
+            auto cC = [&](int m) { return m <= l ? N1(m) * (long double)(l1 + m) / N0(m) : 0.0L; };
+            auto set = [&](int row, int word, bool hi, long double cf, int m) {
+                dtm[(size_t)row * Ll + lm] = (double)(cf / (long double)(2 * l + 3));
+                const int h = l1 * l1 + l1 + m;
+                dti[(size_t)word * Ll + lm] |= (uint16_t)(hi ? h << 8 : h);
+            };
+            if (k > 0) {
+                set(5, 3, false, -cA(k - 1), k - 1);
+                set(6, 3, true, cB(k + 1), k + 1);
+                if (k > 1) set(7, 4, false, cA(k - 1), -(k - 1));
+                set(8, 4, true, cB(k + 1), -(k + 1));
+            } else if (k == 0) {
+                set(6, 3, true, cB(1), 1);
+                set(8, 4, true, cB(1), -1);
+            } else {
+                if (kk > 1) set(5, 3, false, -cA(kk - 1), -(kk - 1));
+                set(6, 3, true, cB(kk + 1), -(kk + 1));
+                set(7, 4, false, -cA(kk - 1), kk - 1);
+                set(8, 4, true, -cB(kk + 1), kk + 1);
+            }
+            set(9, 5, false, cC(kk), k);
+        }
     // one constant buffer: betaC | betaCa | aprime | remainders of betaC, aprime | G | rq | WN | c0 | Nt | gcoef |
     // exp2 table
     std::vector<double> all;
@@ -557,6 +617,9 @@ int upload_constants(soap_ctx *c) {
     size_t o_ja = all.size(); all.insert(all.end(), jab.begin(), jab.end());
     size_t o_jp = all.size(); all.resize(o_jp + (jpq.size() + 3) / 4);
     std::memcpy(all.data() + o_jp, jpq.data(), 2 * jpq.size());
+    size_t o_dt = all.size(); all.insert(all.end(), dtm.begin(), dtm.end());
+    size_t o_di = all.size(); all.resize(o_di + (dti.size() + 3) / 4);
+    std::memcpy(all.data() + o_di, dti.data(), 2 * dti.size());
     hipError_t e;
     if ((e = c->d_const.ensure(all.size() * 8)) != hipSuccess) return hip_fail(c, e, "hipMalloc(constants)");
     if ((e = hipMemcpy(c->d_const.p, all.data(), all.size() * 8, hipMemcpyHostToDevice)) != hipSuccess)
@@ -605,6 +668,8 @@ int upload_constants(soap_ctx *c) {
     P.e2t = d + o_e2;
     P.jab = d + o_ja;
     P.jpq = reinterpret_cast<const uint16_t *>(d + o_jp);
+    P.dtm = d + o_dt;
+    P.dti = reinterpret_cast<const uint16_t *>(d + o_di);
     P.dtab = c->d_dtab.as<uint32_t>();
     P.tri_lw = (int)c->dtab.size();
     c->rtab_kind = 0; // of the previous constants
@@ -708,6 +773,15 @@ size_t quad_bytes(const soap_ctx *c, int64_t first, int64_t count) {
     return quad_bytes_per_edge(c) * (size_t)(c->h_row[first + count] - c->h_row[first]);
 }
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// The density step of the Jacobian path on the matrix cores: its chunks hold one
+// species, so it takes the structures whose rows have MX_MIN_RUN edges or more
+// per species on average.  (One kernel per neighbour list: a center's results do
+// not depend on the batch that computes it.)
+bool use_mx(const soap_ctx *c) {
+    constexpr double MX_MIN_RUN = 8.0;
+    return c->mx_cfg.W > 0 && (double)c->E >= MX_MIN_RUN * (double)c->nc * (double)c->P.S;
+}
 
 Params params_for(const soap_ctx *c, int mode) {
     Params P = c->P;
@@ -871,8 +945,10 @@ int soap_get_option(const soap_ctx *c, const char *key, int64_t *value) {
                {"output_kernel_rows", c->out_plan.rows ? 1 : 0},
                {"jacobian_l_groups", c->groups[1]},
                {"jacobian_density_tile",
-                c->djac_cfg.W > 0 ? c->djac_cfg.W : (c->djs_cfg.W > 0 ? c->djs_cfg.W : c->dens_cfg[1].W)},
-               {"jacobian_density_lds", (int64_t)(c->djac_cfg.W > 0 ? c->djac_cfg.lds
+                use_mx(c) ? c->mx_cfg.W
+                          : (c->djac_cfg.W > 0 ? c->djac_cfg.W : (c->djs_cfg.W > 0 ? c->djs_cfg.W : c->dens_cfg[1].W))},
+               {"jacobian_density_lds", (int64_t)(use_mx(c)           ? c->mx_cfg.lds
+                                                  : c->djac_cfg.W > 0 ? c->djac_cfg.lds
                                                                     : (c->djs_cfg.W > 0 ? c->djs_cfg.lds
                                                                                         : c->dens_cfg[1].lds))},
                {"jacobian_tile", c->eb_cfg.threads > 0 ? 4 * c->eb_cfg.Q : c->jac_cfg.W},
@@ -880,7 +956,7 @@ int soap_get_option(const soap_ctx *c, const char *key, int64_t *value) {
                {"output_lds", (int64_t)c->out_plan.lds},
                {"descriptor_kernel", c->desc_cfg.W > 0 ? 1 : 0},
                // 0 k_density, 1 k_djac, 2 k_djs (then the output kernel)
-               {"jacobian_density_kernel", c->djac_cfg.W > 0 ? 1 : (c->djs_cfg.W > 0 ? 2 : 0)}};
+               {"jacobian_density_kernel", use_mx(c) ? 3 : (c->djac_cfg.W > 0 ? 1 : (c->djs_cfg.W > 0 ? 2 : 0))}};
     for (const auto &t : tab)
         if (!std::strcmp(key, t.k)) {
             *value = t.v;
@@ -1200,7 +1276,7 @@ int soap_get_neighbors(soap_ctx *c, int64_t *row_ptr_dev, int32_t *cols_dev, voi
 // l into groups; the one-workgroup-per-center kernel needs neither split)
 static bool jacobian_path_ok(const soap_ctx *c, int mode) {
     if (mode == 1 && c->djac_cfg.W > 0) return c->jac_ok;
-    if (mode == 1 && c->djs_cfg.W > 0) return c->jac_ok && c->out_ok;
+    if (mode == 1 && (c->djs_cfg.W > 0 || use_mx(c))) return c->jac_ok && c->out_ok;
     return c->dens_ok[mode] && (mode != 1 || (c->jac_ok && (c->groups[1] == 1 || c->out_ok)));
 }
 
@@ -1266,7 +1342,7 @@ static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void
         timer.done();
         return SOAP_OK;
     }
-    if (mode == 1 && c->djac_cfg.W > 0) { // one workgroup per center
+    if (mode == 1 && c->djac_cfg.W > 0 && !use_mx(c)) { // one workgroup per center
         DjacLaunch dj = c->djac_cfg;
         if (wg_per_cu > 0) {
             int ncu = 256;
@@ -1276,6 +1352,21 @@ static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void
         hipError_t e = launch_djac(P, rows_of(c, first, count), c->pos, c->built_f64, c->ar64, dj, desc, jself,
                                    scratch, to_stream(stream));
         if (e != hipSuccess) return hip_fail(c, e, "density kernel");
+        timer.done();
+        return SOAP_OK;
+    }
+    if (mode == 1 && use_mx(c)) { // one workgroup per center, then the output kernel
+        DensityMxLaunch mx = c->mx_cfg;
+        if (wg_per_cu > 0) {
+            int ncu = 256;
+            (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+            mx.blocks = std::max(1, std::min(mx.blocks, ncu * wg_per_cu));
+        }
+        hipError_t e = launch_density_mx(P, rows_of(c, first, count), c->pos, c->built_f64, c->ar64, mx, scratch,
+                                         to_stream(stream));
+        if (e != hipSuccess) return hip_fail(c, e, "density kernel");
+        e = launch_outputs(P, c->out_plan, count, c->built_f64, scratch, desc, jself, to_stream(stream));
+        if (e != hipSuccess) return hip_fail(c, e, "output kernel");
         timer.done();
         return SOAP_OK;
     }

@@ -1925,11 +1925,12 @@ __global__ __launch_bounds__(BSC) void k_djac(Params P, Rows R, const PosT *__re
 // Task t is radial pair t % np of harmonic lm = t / np, so that neighbouring
 // threads own neighbouring entries of a scratch row.
 // ---------------------------------------------------------------------------
-// the real solid harmonics of columns m = m0, m0 + ms, ... (lane = edge; the
-// column recurrence of sh_all_lane, (x + i y)^m advanced by (x + i y)^ms)
+// the real solid harmonics of columns m = m0 + g ms, m0 + (g + ng) ms, ... (lane =
+// edge; the column recurrence of sh_all_lane, (x + i y)^m advanced by (x + i
+// y)^ms one step at a time, so that the values do not depend on ng)
 template <typename YT>
 __device__ __forceinline__ void sh_cols_lane(double x, double y, double z, const double *__restrict__ Nt, int ldN,
-                                             int lw, YT *__restrict__ Y, int ls, int m0, int ms) {
+                                             int lw, YT *__restrict__ Y, int ls, int m0, int ms, int g, int ng) {
     const double r2 = x * x + y * y + z * z;
     double c = 1.0, s = 0.0, cs = 1.0, ss = 0.0;
     for (int k = 0; k < m0; ++k) {
@@ -1942,7 +1943,12 @@ __device__ __forceinline__ void sh_cols_lane(double x, double y, double z, const
         ss = x * ss + y * cs;
         cs = cn;
     }
-    for (int m = m0; m < lw; m += ms) {
+    for (int k = 0; k < g; ++k) {
+        const double cn = c * cs - s * ss;
+        s = c * ss + s * cs;
+        c = cn;
+    }
+    for (int m = m0 + g * ms; m < lw; m += ms * ng) {
         double R1 = 0.0, R = 1.0; // R_{l-1}, R_l
         for (int l = m; l < lw; ++l) {
             if (l > m) {
@@ -1960,9 +1966,11 @@ __device__ __forceinline__ void sh_cols_lane(double x, double y, double z, const
                 Y[(o - m) * ls] = (YT)(v * s);
             }
         }
-        const double cn = c * cs - s * ss;
-        s = c * ss + s * cs;
-        c = cn;
+        for (int k = 0; k < ng; ++k) {
+            const double cn = c * cs - s * ss;
+            s = c * ss + s * cs;
+            c = cn;
+        }
     }
 }
 
@@ -2117,7 +2125,7 @@ __global__ __launch_bounds__(BSC) void k_djs(Params P, Rows R, const PosT *__res
                 }
             }
             stage_radial<ST>(P, cs - rad0, nb, tid, Bl, Hl, ldl, WP);
-            if (lane < nb) sh_cols_lane(gx, gy, gz, Nt, ldN, lw, Yl + lane, WP, wave, NWC);
+            if (lane < nb) sh_cols_lane(gx, gy, gz, Nt, ldN, lw, Yl + lane, WP, wave, NWC, 0, 1);
             lds_barrier();
             // ---- projection, thread = (radial pair, lm), species run by run ----
             for (int s = 0; s < S; ++s) {

@@ -43,6 +43,8 @@ struct Params {
     const double *gcoef;       // [(l, m >= 0)][4] gradient identities of the harmonics (cA, cB, cC, l | m << 8)
     const double *jab;         // rows of the edge Jacobian's products (jacobian_blocks.hip): alpha [4][L + 3], beta [2][L + 3]
     const uint16_t *jpq;       // and p | q << 8 [4][L + 3]
+    const double *dtm;         // density step (density_matrix.hip): T- and T+ [10][L]
+    const uint16_t *dti;       // and their harmonics, p | q << 8 [6][L]
     const uint32_t *dtab;      // [tri_lw] diagonal-pair slots: (n lw + l) | (n' lw + l) << 16, n' >= n
     int tri_lw;                // n (n + 1) / 2 * (l_max + 1)
     int n_groups;              // l-groups of the density kernel
@@ -175,6 +177,11 @@ struct DjsLaunch {
     size_t lds;
     int blocks;     // resident workgroups (persistent launch)
 };
+struct DensityMxLaunch {
+    int W;          // edges per chunk (0: not used)
+    size_t lds;
+    int blocks;     // resident workgroups (persistent launch)
+};
 struct JacLaunch {
     int W;          // edges per wave tile (at most jacobian_max_w())
     size_t lds;
@@ -272,6 +279,14 @@ int djs_blocks_per_cu(bool f64, bool ar64, int qt, size_t lds);
 hipError_t launch_djs(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64, const DjsLaunch &cfg,
                       void *c_scratch, hipStream_t st);
 hipError_t djs_set_lds_limit(int lim);
+// the same on the matrix cores, one species per chunk (density_matrix.hip)
+const void *density_mx_0(int n, int lmax);
+const void *density_mx_1(int n, int lmax);
+const void *density_mx_2(int n, int lmax);
+size_t density_mx_lds(const Params &P, int W, bool st64);
+int density_mx_blocks_per_cu(const Params &P, bool f64, bool ar64, size_t lds);
+hipError_t launch_density_mx(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64,
+                             const DensityMxLaunch &cfg, void *c_scratch, hipStream_t st);
 // column means of a row-major (rows x cols) array of the output type, in
 // float64: part[AVG_CHUNKS][cols] partial sums, then mean[cols] (float64)
 // and, if out is not NULL, out[cols] at the output type

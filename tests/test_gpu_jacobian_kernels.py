@@ -1,0 +1,104 @@
+"""The kernels of the Jacobian path's larger bases against the oracle, at the
+sizes where they can go wrong: the radial pass (table and direct), the edge
+Jacobian kernel of eight-edge chunks, the density step on the matrix cores."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_05709_amd import workloads
+from tests.parity import TOL, gpu_run, jacobian_errors, row_errors
+
+pytestmark = pytest.mark.gpu
+
+MODES = [("float32", "mixed"), ("float32", "fp64"), ("float64", "mixed")]
+
+
+def _check(wl, st, dtype, arith="mixed", centers=None):
+    print(f"[kernels] {wl.name} {dtype} {arith}", flush=True)
+    g = gpu_run(wl, st, dtype, centers=centers, arith=arith)
+    idx = np.arange(st.n_atoms) if centers is None else np.asarray(centers)
+    ref = oracle.OracleSOAP(wl.species, wl.r_cut, wl.n_max, wl.l_max, wl.sigma, wl.rbf).compute(
+        st.pos64, st.Z, centers=idx, jacobian=True)
+    ed = row_errors(g["desc"], ref["desc"]).max()
+    ej = jacobian_errors(g, ref, st, wl.species, range(len(idx)), idx)
+    print(f"[kernels] {wl.name} {dtype} {arith}: desc {ed:.2e} jac {ej:.2e}", flush=True)
+    assert ed < TOL[dtype] and ej < TOL[dtype]
+
+
+def _wl(species, rbf, n, l, r_cut=4.5, sigma=0.5):
+    return workloads.Workload(f"s{len(species)}_{rbf}_n{n}l{l}", tuple(species), rbf, r_cut, sigma, n, l, True,
+                              ("none",))
+
+
+# (species, n, l): one and two matrix-core column tiles at their edges (S n = 15,
+# 16, 18, 32, 33, 64), one degree, the last
+# degree, odd and even degree counts, one radial function
+BASES = [((1,), 1, 0), ((1,), 1, 1), ((1,), 15, 3), ((1, 8), 8, 4), ((1, 8), 9, 5), ((1, 8), 16, 2),
+         ((1, 6, 8), 11, 6), ((1, 6, 7, 8), 16, 3), ((1, 8), 5, 14), ((1, 8), 12, 13)]
+
+
+@pytest.mark.parametrize("dtype,arith", MODES)
+@pytest.mark.parametrize("species,n,l", BASES)
+def test_basis_edges(species, n, l, dtype, arith):
+    """Rows from none to some tens of neighbours, so chunks of one to eight
+    edges and species runs of every remainder."""
+    st = workloads.random_small(40, 7 + n, 4.0, species=species, dmin=0.9)
+    st.pos[-1] += np.float32(40.0)  # one atom without neighbours
+    _check(_wl(species, "polynomial", n, l), st, dtype, arith)
+
+
+@pytest.mark.parametrize("dtype,arith", MODES)
+def test_long_rows(dtype, arith):
+    """Rows longer than one row block of the edge Jacobian kernel (128 edges)
+    and than one chunk per species of the density step (64)."""
+    st = workloads.random_small(330, 5, 4.6, species=(1, 8), dmin=0.7)
+    _check(_wl((1, 8), "polynomial", 8, 7, r_cut=5.0), st, dtype, arith, centers=[0, 11, 200, 329])
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("rbf,sigma", [("polynomial", 0.5), ("polynomial", 0.3), ("gto", 0.5),
+                                       ("gto", 0.02), ("polynomial-laplace", 0.3)])
+def test_radial_pass_distances(rbf, sigma, dtype):
+    """Dimers over every distance: coincident, nearly so, at the table's
+    interval boundaries and around them, up to the last value below the
+    cutoff.  sigma 0.02 has no table (too many intervals;
+    the oracle's Bessel functions end before the quadrature's would); the Laplace form
+    never has one and starts where it is an expansion at all."""
+    rc = 5.0
+    h = rc / np.ceil(rc / sigma * 20.0)
+    last = float(np.nextafter(np.float32(rc), np.float32(0)))
+    d = [0.5, 1.0, 2.345, h * 40, np.nextafter(h * 40, 0), np.nextafter(h * 40, 9), rc - h / 2, last]
+    if rbf != "polynomial-laplace":
+        d += [0.0, 1e-3, 0.05, h, h / 3]
+    pos, Z = [], []
+    for k, r in enumerate(d):  # the x coordinates start at 0, so that r is the exact float32 distance
+        pos += [[0.0, 20.0 * k, 0.0], [r, 20.0 * k, 0.0]]
+        Z += [1, 8]
+    st = workloads.Structure(np.array(pos, dtype=np.float32), np.array(Z, dtype=np.int32), 0.0, 0)
+    _check(_wl((1, 8), rbf, 10 if rbf == "gto" else 6, 12 if rbf == "gto" else 5, r_cut=rc, sigma=sigma), st, dtype)
+
+
+@pytest.mark.parametrize("dtype,arith", MODES)
+@pytest.mark.parametrize("n,l", [(4, 12), (10, 10), (12, 6)])
+def test_density_step_matrix_and_shared(n, l, dtype, arith):
+    """The density step on the matrix cores (rows of eight and more edges per
+    species) and the shared density kernel (djs_tile -1) on the same rows."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    st = workloads.water_cluster(64, 0)
+    tdt = torch.float64 if dtype == "float64" else torch.float32
+    pos, Z = torch.from_numpy(st.pos).to("cuda", tdt), torch.from_numpy(st.Z).cuda()
+    out = []
+    for tile in (0, -1):
+        sp = Soap((1, 8), 5.0, n, l, 0.5, "polynomial", dtype=dtype, arith=arith)
+        sp.set_option("djs_tile", tile)
+        sp.build_neighbors(pos, Z)
+        assert sp.get_option("jacobian_density_kernel") == (3 if tile == 0 else 0)
+        out.append([t.double() for t in sp.derivatives()])
+        again = sp.derivatives()
+        assert all(torch.equal(a.double(), b) for a, b in zip(again, out[-1]))
+        sp.close()
+    for a, b in zip(*out):
+        scale = b.abs().flatten(1).max(1).values
+        err = (a - b).abs().flatten(1).max(1).values
+        assert torch.all(err <= TOL[dtype] * scale)
