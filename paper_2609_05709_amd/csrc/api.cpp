@@ -1463,7 +1463,8 @@ static hipError_t run_jacobian(const soap_ctx *c, int64_t first, int64_t cf, int
     const Params P = params_for(c, 1);
     const Rows R = rows_part(c, first, cf, cn);
     if (c->eb_cfg.threads > 0)
-        return launch_edge_blocks(P, R, c->pos, c->built_f64, c->ar64, c->eb_cfg, scratch, jac_edge, st);
+        return launch_edge_blocks(P, R, c->pos, c->built_f64, c->ar64, c->eb_cfg, (double)c->E / (double)c->nc, scratch,
+                                  jac_edge, st);
     return launch_jacobian(P, R, c->pos, c->built_f64, c->ar64, c->jac_cfg, scratch, jac_edge, st);
 }
 

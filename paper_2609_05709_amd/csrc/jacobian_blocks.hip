@@ -31,6 +31,8 @@
 // l_max 6: 0.49 against 0.57.
 #include "soap_device.h"
 
+#include <cmath>
+
 namespace soap {
 using namespace dev;
 namespace dev {
@@ -339,18 +341,27 @@ bool eb_plan(const Params &P, bool f64, bool ar64, EdgeBlocksLaunch *out) {
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, 64 * nw, lds) != hipSuccess) continue;
             if (nb * nw > best) {
                 best = nb * nw;
-                *out = EdgeBlocksLaunch{Q, RB, 1, 64 * nw, lds};
+                *out = EdgeBlocksLaunch{Q, RB, 64 * nw, lds};
             }
         }
     return best > 0;
 }
 
 hipError_t launch_edge_blocks(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64,
-                              const EdgeBlocksLaunch &cfg, const void *c_scratch, void *jedge, hipStream_t st) {
+                              const EdgeBlocksLaunch &cfg, double degree, const void *c_scratch, void *jedge,
+                              hipStream_t st) {
     if (R.nc <= 0) return hipSuccess;
     Params Pk = P;
     Rows Rk = R;
-    int Q = cfg.Q, RB = cfg.RB, split = cfg.split;
+    // Few centers: several workgroups per center, each some of its chunks, until
+    // about four workgroups per CU (what stays resident) have work (64-water
+    // cluster, n_max 4, l_max 4: 41 us with one workgroup per center, 24 with
+    // three); more centers gain nothing and load their tables again.
+    int ncu = 256, dev_id = 0;
+    (void)hipGetDevice(&dev_id);
+    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev_id);
+    const int64_t want = (4 * (int64_t)ncu) / R.nc, chunks = (int64_t)std::ceil(degree / (4.0 * cfg.Q));
+    int Q = cfg.Q, RB = cfg.RB, split = (int)std::max<int64_t>(1, std::min(want, chunks));
     void *args[] = {&Pk, &Rk, &pos, &Q, &RB, &split, &c_scratch, &jedge};
     return hipLaunchKernel(eb_kernel(f64, ar64, P.lmax + 1), dim3((unsigned)(R.nc * split)), dim3(cfg.threads), args, cfg.lds, st);
 }

@@ -262,13 +262,13 @@ hipError_t launch_jacobian(const Params &P, const Rows &R, const void *pos, bool
 struct EdgeBlocksLaunch {
     int Q;       // quads of edges per chunk (0: not used)
     int RB;      // edges per row block
-    int split;   // workgroups per center
     int threads;
     size_t lds;
 };
 bool eb_plan(const Params &P, bool f64, bool ar64, EdgeBlocksLaunch *out);
 hipError_t launch_edge_blocks(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64,
-                              const EdgeBlocksLaunch &cfg, const void *c_scratch, void *jedge, hipStream_t st);
+                              const EdgeBlocksLaunch &cfg, double degree, const void *c_scratch, void *jedge,
+                              hipStream_t st); // degree: edges per center, about
 hipError_t eb_set_lds_limit(int lim);
 // density step of the Jacobian path with the coefficients streamed to the
 // scratch (k_djs, density_streamed.hip): bases of at most four (radial pair,
