@@ -800,32 +800,35 @@ __device__ __forceinline__ void power_tiles(const CoefView<CT> cv, int comp, int
             }
         }
         const int ua = 16 * ti + ro, vb = 16 * tj + ro; // A row, B column of this lane
-        const bool uok = ua < Sn, vok = vb < Sn;
-        const int oa = (uok ? ua : 0) * cv.ldu + (l * l - lm0) * cv.ldm;
-        const int ob = (vok ? vb : 0) * cv.ldu + (l * l - lm0) * cv.ldm;
+        // Operands past S n read u = 0: they enter rows and columns that are not
+        // stored.  m runs in chunks of four, the last one short: there, and
+        // only there, the operands are masked (both: 0 times an infinite
+        // coefficient would be NaN) and m clamped.
+        const int base = (l * l - lm0) * cv.ldm, mstep = 4 * cv.ldm, nfull = l >> 1;
+        const int oa = (ua < Sn ? ua : 0) * cv.ldu + base, ob = (vb < Sn ? vb : 0) * cv.ldu + base;
+        const bool mok = kk <= 2 * l - 4 * nfull;
+        const int ml = nfull * mstep + (mok ? kk : 0) * cv.ldm;
         dbl4 acc = {0.0, 0.0, 0.0, 0.0};
         // one loop per kind (comp is uniform): a branch inside the chain made
         // the two kinds' accumulators meet in copies at every chunk
         if (comp < 0) {
-            for (int ch = 0; ch < (l >> 1) + 1; ++ch) {
-                const int m = 4 * ch + kk;
-                const bool mok = m <= 2 * l;
-                const int mo = (mok ? m : 0) * cv.ldm;
-                const double ca = (double)cv.C[oa + mo], cb = (double)cv.C[ob + mo];
-                const double xa = (mok && uok) ? ca : 0.0, xb = (mok && vok) ? cb : 0.0;
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa, xb, acc, 0, 0, 0);
-            }
+            const CT *pa = cv.C + oa + kk * cv.ldm, *pb = cv.C + ob + kk * cv.ldm;
+            for (int ch = 0; ch < nfull; ++ch, pa += mstep, pb += mstep)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)*pa, (double)*pb, acc, 0, 0, 0);
+            const double xa = (double)cv.C[oa + ml], xb = (double)cv.C[ob + ml];
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(mok ? xa : 0.0, mok ? xb : 0.0, acc, 0, 0, 0);
         } else {
-            for (int ch = 0; ch < (l >> 1) + 1; ++ch) {
-                const int m = 4 * ch + kk;
-                const bool mok = m <= 2 * l;
-                const int mo = (mok ? m : 0) * cv.ldm;
-                const double ca = (double)cv.C[oa + mo], cb = (double)cv.C[ob + mo];
-                const double xa = (mok && uok) ? ca : 0.0, xb = (mok && vok) ? cb : 0.0;
-                const double da = (double)cv.D[oa + mo], db = (double)cv.D[ob + mo];
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((mok && uok) ? da : 0.0, xb, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa, (mok && vok) ? db : 0.0, acc, 0, 0, 0);
+            int ia = oa + kk * cv.ldm, ib = ob + kk * cv.ldm;
+            for (int ch = 0; ch < nfull; ++ch, ia += mstep, ib += mstep) {
+                const double xa = (double)cv.C[ia], xb = (double)cv.C[ib];
+                const double da = (double)cv.D[ia], db = (double)cv.D[ib];
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(da, xb, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa, db, acc, 0, 0, 0);
             }
+            const double xa = (double)cv.C[oa + ml], xb = (double)cv.C[ob + ml];
+            const double da = (double)cv.D[oa + ml], db = (double)cv.D[ob + ml];
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(mok ? da : 0.0, mok ? xb : 0.0, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(mok ? xa : 0.0, mok ? db : 0.0, acc, 0, 0, 0);
         }
         // lane holds rows u = 16 ti + kk + 4 r of column v = 16 tj + ro
         const double K = comp < 0 ? Kl[l] : -Kl[l];
