@@ -137,7 +137,8 @@ def measured_traffic(workload_name, kernel, output):
         return None
 
 
-KERNEL_SOURCES = ("soap_device.h", "soap_kernels.hip", "density_streamed.hip", "jacobian_fixed.hip", "soap_internal.h")
+KERNEL_SOURCES = ("soap_device.h", "soap_kernels.hip", "density_streamed.hip", "density_matrix.hip", "jacobian_blocks.hip",
+                  "jacobian_fixed.hip", "radial.hip", "soap_internal.h")
 
 
 def kernels_source_sha():
@@ -360,6 +361,7 @@ def run(wl, steps, warmup, dtype, with_cpu=True, quiet=False, mode="derivatives"
     # the kernels the library's plan chose for this basis
     desc_kernel = "k_desc" if sp.get_option("descriptor_kernel") else "k_density"
     dens_kernel = ("k_density", "k_djac", "k_djs", "k_density_mx")[int(sp.get_option("jacobian_density_kernel"))]
+    jac_kernel = "k_edge_blocks" if sp.get_option("jacobian_kernel") else "k_jacobian"
     # per step (a pipelined step launches its kernels once per center chunk;
     # the chunks' Jacobian launches then overlap the density launches)
     kern = {"neighbors": seg_ms[0] / steps, "density": seg_ms[1] / steps, "jacobian": seg_ms[2] / steps,
@@ -375,10 +377,10 @@ def run(wl, steps, warmup, dtype, with_cpu=True, quiet=False, mode="derivatives"
     elif jac:
         # the edge-block writes dominate: HBM-bound kernel
         t = kern["jacobian"] * 1e-3
-        roof = {"kernel": "k_jacobian", "bound": "hbm", "achieved": alg["jacobian"] / t / 1e9, "peak": HBM_PEAK_GBS,
+        roof = {"kernel": jac_kernel, "bound": "hbm", "achieved": alg["jacobian"] / t / 1e9, "peak": HBM_PEAK_GBS,
                 "unit": "GB/s",
                 # the counters were taken on the default (mixed-arithmetic) kernels
-                "traffic": None if periodic or arith != "mixed" else measured_traffic(wl.name, "k_jacobian", dtype),
+                "traffic": None if periodic or arith != "mixed" else measured_traffic(wl.name, jac_kernel, dtype),
                 "alg_bytes_per_launch": alg["jacobian"]}
     else:
         fl = density_flops(wl, E, nc, sp.n_features)

@@ -170,8 +170,7 @@ int soap_create(const int32_t *species_Z, int32_t n_species, double r_cut, int32
  *              many, one after another on the stream, so that the library's
  *              scratch (the coefficients c, D of the Jacobian path:
  *              4 S n_max (l_max+1)^2 values per center, float32 in the mixed
- *              arithmetic and float64 otherwise, and the polynomial
- *              quadrature's radial factors) is sized for one batch (Sec. 3.3:
+ *              arithmetic and float64 otherwise) is sized for one batch (Sec. 3.3:
  *              center batches bound the memory of one call); the outputs are
  *              the same arrays, bit for bit, as in one batch;
  *   "pipeline" : 1..16 (default 1): soap_derivatives splits its centers
@@ -195,6 +194,8 @@ int soap_set_option(soap_ctx *ctx, const char *key, int64_t value);
  *   "descriptor_kernel"       : 1 if soap_compute / soap_coefficients run the
  *                               descriptor kernel that gives each center a
  *                               workgroup, 0 if the shared density kernel;
+ *   "jacobian_kernel" : the edge Jacobian of soap_derivatives: 0 k_jacobian,
+ *              1 k_edge_blocks;
  *   "jacobian_density_kernel" : the density step of soap_derivatives: 1 the
  *                               kernel that gives each center a workgroup and
  *                               writes its outputs ("djac_tile"), 2 the one
@@ -413,7 +414,8 @@ int soap_derivatives_batch(soap_ctx *ctx, int64_t first, int64_t count, void *de
  * buffer.  This call allocates nothing and records no timing events; the
  * neighbour list must already be built (soap_build_neighbors allocates).
  * Limit: count * 4 S n_max (l_max+1)^2 scratch values (4 bytes each in the
- * mixed arithmetic, else 8; plus the polynomial quadrature's radial factors)
+ * mixed arithmetic, else 8; plus 16 n_max (l_max+1) bytes per edge for the
+ * polynomial quadrature)
  * <= SOAP_STATIC_SCRATCH_BYTES (e.g. 5349 centers of the 2-species n_max 8,
  * l_max 6 basis in the mixed arithmetic, 2674 in float64), else
  * SOAP_ECAPACITY with nothing enqueued; larger structures go through in

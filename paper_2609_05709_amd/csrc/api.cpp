@@ -956,6 +956,7 @@ int soap_get_option(const soap_ctx *c, const char *key, int64_t *value) {
                {"output_lds", (int64_t)c->out_plan.lds},
                {"descriptor_kernel", c->desc_cfg.W > 0 ? 1 : 0},
                // 0 k_density, 1 k_djac, 2 k_djs (then the output kernel)
+               {"jacobian_kernel", c->eb_cfg.threads > 0}, // 0 k_jacobian, 1 k_edge_blocks
                {"jacobian_density_kernel", use_mx(c) ? 3 : (c->djac_cfg.W > 0 ? 1 : (c->djs_cfg.W > 0 ? 2 : 0))}};
     for (const auto &t : tab)
         if (!std::strcmp(key, t.k)) {

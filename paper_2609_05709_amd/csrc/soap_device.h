@@ -347,7 +347,7 @@ __host__ __device__ __forceinline__ size_t table_doubles(const Params &P, int lg
     if (P.rbf == 0) d += 2 * (size_t)lgc * n * n + even((size_t)lgc * n);
     else if (P.rbf == 2) d += 4 * n * (n + 3) + even(n);
     else if (P.rbf == 3) d += 2 * (size_t)lgc * n * n + 2 * (size_t)lgc * n;
-    return d; // the polynomial quadrature reads its radial factors from k_radial: no tables
+    return d; // RBF_BUFFERED reads its radial factors from the radial pass: no tables
 }
 
 // RBF: the radial basis fixed at compile time (0 GTO), or -1 to read it from P
@@ -413,7 +413,7 @@ __device__ __forceinline__ void load_tables(const Params &P, Carver &cv, Tables 
 }
 
 // X scratch per edge: GTO exponentials n * lgc; none for the polynomial
-// quadrature (its radial factors come from k_radial); Laplace form: the four
+// quadrature (its radial factors come from the radial pass); Laplace form: the four
 // l-independent values P_j per n, 4 n; compensated GTO: the exponentials in
 // double-double, 2 n * lgc
 __host__ __device__ __forceinline__ size_t stage_x_doubles(const Params &P, int lgc, int lg1) {
@@ -1587,8 +1587,9 @@ __global__ __launch_bounds__(BSC) void k_desc(Params P, Rows R, const PosT *__re
 }
 
 // ---------------------------------------------------------------------------
-// k_djac: the density step of the Jacobian path for the GTO basis, in the
-// layout of k_desc (one center per workgroup of NWC waves, 64-edge chunks,
+// k_djac: the density step of the Jacobian path, with its own radial factors
+// (GTO) or the radial pass's (RBF_BUFFERED, whose staging copies them instead
+// of running the tasks l), in the layout of k_desc (one center per workgroup of NWC waves, 64-edge chunks,
 // staging lane = edge split over the waves by task, every accumulated entry
 // owned by one thread):
 //   staging: task l: B_nl and Bh_nl = (1/r) dB_nl/dr = sum_k betaCa e_kl
@@ -1915,13 +1916,11 @@ __global__ __launch_bounds__(BSC) void k_djac(Params P, Rows R, const PosT *__re
 // written once, by its owner; a species without neighbours gets zeros, and c
 // of the center's own species its on-site term).  The output kernel then
 // writes the power spectrum and the center block from the scratch, and
-// k_jacobian reads c from it.
+// the edge Jacobian kernel reads c from it.
 //   staging: the chunk's edge vectors and species (wave 0); the radial
-//     factors B_nl, Bh_nl: GTO (RBF 0) from the exponentials as in k_djac,
-//     one l per task over the waves; polynomial quadrature (RBF 1) copied
-//     from the factors k_radial left for the call's edges, all threads, in
-//     the buffer's order; the solid harmonics, their columns m spread over
-//     the waves (sh_cols_lane);
+//     factors B_nl, Bh_nl, copied from those the radial pass left for the
+//     call's edges, all threads, in their order; the solid harmonics, their
+//     columns m spread over the waves (sh_cols_lane);
 //   projection: thread = (radial pair, lm), per edge
 //       c_{a lm} += B_al S_lm,  D_{a lm} += Bh_al r S_lm + B_al grad S_lm,
 //     each sum in row order (deterministic with no ordering protocol).
