@@ -1,6 +1,6 @@
 // The radial pass: the radial factors (B_nl, Bh_nl) of every edge of a range
-// of centers, evaluated once per call for every basis and read by the density
-// and Jacobian kernels of the call.  Evaluated inside those kernels, they
+// of centers, evaluated once per call and read by the density and Jacobian
+// kernels of the call (all bases but those whose kernels evaluate their own).  Evaluated inside those kernels, they
 // were computed twice per edge, in tiles of a few edges that filled a wave
 // badly and held the basis tables in the kernels' LDS; here the items
 // (edge, degree) run flat over all lanes.
@@ -69,7 +69,9 @@ __host__ __device__ __forceinline__ size_t radial_flat_lds_doubles(const Params 
 // form (radial index, edge) - with the edge running fastest, so that the
 // basis coefficients a wave reads are broadcast.  The results go through LDS:
 // an edge's pairs leave as one contiguous run (204,662 edges, n_max 8, l_max 6:
-// 96 us stored per item, 55 through an LDS tile).
+// 96 us stored per item, 55 through an LDS tile).  An edge of length 0 has only
+// its factors B_n0, its on-site term: the density step on the matrix cores takes
+// the others as they are, and their gradients would enter its center's D.
 template <typename PosT, typename ST, int NA, int RBF>
 __global__ __launch_bounds__(BSR) void k_radial_flat(Params P, Rows R, const PosT *__restrict__ pos, int cb) {
     extern __shared__ __align__(16) double smem[];
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(BSR) void k_radial_flat(Params P, Rows R, const Pos
                             b += bc[a * NA + k] * ex[k];
                             h += bc[a * NA + k] * ea[k];
                         }
-                        o[a * lw + q] = Pair<ST>::make(b, h);
+                        o[a * lw + q] = d2 == 0.0 ? Pair<ST>::make(q == 0 ? b : 0.0, 0.0) : Pair<ST>::make(b, h);
                     }
                 } else if constexpr (RBF == 3) {
 #pragma clang fp contract(off)
@@ -175,7 +177,8 @@ __global__ __launch_bounds__(BSR) void k_radial_flat(Params P, Rows R, const Pos
                             cb2 += (fma(cx, ex[k].hi, -pb) + tb.lo) + (cx * ex[k].lo + cy * ex[k].hi);
                             ch += (fma(m.hi, ex[k].hi, -ph) + th.lo) + (m.hi * ex[k].lo + m.lo * ex[k].hi);
                         }
-                        o[a * lw + q] = Pair<ST>::make(sb + cb2, -2.0 * (sh + ch));
+                        const double b = sb + cb2, h = -2.0 * (sh + ch);
+                        o[a * lw + q] = d2 == 0.0 ? Pair<ST>::make(q == 0 ? b : 0.0, 0.0) : Pair<ST>::make(b, h);
                     }
                 } else {
                     // Laplace form: the P_j(u) = d^j/du^j sum_k WN_nk u^(k+2), u =

@@ -31,7 +31,8 @@ struct Params {
     const double *WN;          // polynomial, Laplace form [n][n+3][4]: Chebyshev series of P_n0..P_n3 on [0, rc]
     const void *rad;           // radial factors of a range's edges (the radial pass): edge e has its pairs
                                // (B_nl, Bh_nl), [n][l] at the staging precision, at byte (e - *rad_origin) *
-                               // rad_stride (4-byte aligned: they may lie in the edge's Jacobian block)
+                               // rad_stride (4-byte aligned: they may lie in the edge's Jacobian block); an
+                               // edge of length 0 has its B_n0 and zeros
     int64_t rad_stride;        // bytes per edge
     const int64_t *rad_origin; // row offset of the range's first center
     const void *rtab;          // table of the radial factors (radial.hip; NULL: none), records [interval][n][l]

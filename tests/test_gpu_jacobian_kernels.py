@@ -55,6 +55,32 @@ def test_long_rows(dtype, arith):
     _check(_wl((1, 8), "polynomial", 8, 7, r_cut=5.0), st, dtype, arith, centers=[0, 11, 200, 329])
 
 
+@pytest.mark.parametrize("dtype,arith,rbf,n,l,sigma",
+                         [("float32", "fp64", "gto", 8, 8, 0.5),    # factors evaluated directly
+                          ("float64", "mixed", "gto", 8, 12, 0.5),
+                          ("float64", "mixed", "gto", 12, 6, 0.5),  # compensated
+                          ("float32", "mixed", "gto", 9, 9, 0.02),  # too many intervals for a table
+                          ("float32", "mixed", "gto", 9, 9, 0.5),   # from the table
+                          ("float64", "mixed", "polynomial", 8, 8, 0.5),
+                          ("float32", "mixed", "polynomial-laplace", 8, 8, 0.5)])
+def test_coincident_neighbours_in_dense_rows(dtype, arith, rbf, n, l, sigma):
+    """Atoms at one place in rows long enough for the density step on the matrix
+    cores: a zero-length edge is an on-site term with a zero gradient, whichever
+    evaluation the radial factors come from."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    st = workloads.random_small(40, 3, 4.0, species=(1, 8), dmin=0.9)
+    st.pos[7] = st.pos[3]
+    st.pos[20] = st.pos[21]
+    wl = _wl((1, 8), rbf, n, l, r_cut=6.0, sigma=sigma)
+    sp = Soap(wl.species, wl.r_cut, n, l, sigma, rbf, dtype=dtype, arith=arith)
+    sp.build_neighbors(torch.from_numpy(st.pos).to("cuda", torch.float64 if dtype == "float64" else torch.float32),
+                       torch.from_numpy(st.Z).cuda())
+    assert sp.get_option("jacobian_density_kernel") == 3
+    sp.close()
+    _check(wl, st, dtype, arith)
+
+
 @pytest.mark.parametrize("dtype", ["float32", "float64"])
 @pytest.mark.parametrize("rbf,sigma", [("polynomial", 0.5), ("polynomial", 0.3), ("gto", 0.5),
                                        ("gto", 0.02), ("polynomial-laplace", 0.3)])
