@@ -331,6 +331,11 @@ int plan_launches(soap_ctx *c) {
             const size_t lds = jacobian_lds_bytes(Pj, W, st64);
             if (lds > LDS_HARD_LIMIT) continue;
             int b = jacobian_blocks_per_cu(f64, ar64, Pj.rbf, P.n, P.lmax + 1, lds);
+            // a fourth float64 workgroup gains less than the wider tile it is
+            // bought with loses (GTO n_max 4, l_max 5, 24 waters: two-edge tiles
+            // in four workgroups 59 us, three-edge tiles in three 44; n_max 5,
+            // l_max 5, 160 waters: 86 and 68)
+            if (f64) b = std::min(b, 3);
             if (W >= 2 && b >= 2) b *= 2;
             if (b > best) {
                 best = b;

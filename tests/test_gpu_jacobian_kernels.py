@@ -128,3 +128,13 @@ def test_density_step_matrix_and_shared(n, l, dtype, arith):
         scale = b.abs().flatten(1).max(1).values
         err = (a - b).abs().flatten(1).max(1).values
         assert torch.all(err <= TOL[dtype] * scale)
+
+
+@pytest.mark.parametrize("n,l,tile", [(4, 5, 3), (5, 5, 3), (8, 3, 3), (3, 6, 3), (2, 2, 4), (8, 6, 2)])
+def test_float64_tile_plan(n, l, tile):
+    """The float64 edge Jacobian kernel takes the widest tile that keeps three
+    workgroups per CU, not a narrower one for the sake of a fourth."""
+    from paper_2609_05709_amd.soap import Soap
+    sp = Soap((1, 8), 5.5, n, l, 0.5, "gto", dtype="float64")
+    assert (sp.get_option("jacobian_kernel"), sp.get_option("jacobian_tile")) == (0, tile)
+    sp.close()
