@@ -455,7 +455,7 @@ int plan_launches(soap_ctx *c) {
             c->rtab_kind = kind;
         }
         P.rtab = c->b_rtab.p;
-        P.rtab_inv_h = (double)P.rtab_k / c->r_cut;
+        P.rtab_inv_h = radial_table_inv_h(P, st64);
     }
     return SOAP_OK;
 }

@@ -233,26 +233,61 @@ __global__ __launch_bounds__(BSR) void k_radial_flat(Params P, Rows R, const Pos
 // ---------------------------------------------------------------------------
 // The radial factors from a table: on each of rtab_k equal intervals of
 // [0, r_cut] the polynomial through the factors at Chebyshev points, in t =
-// 2 (r - r_left) / h - 1.  Every B_nl and Bh_nl is a function smoothed by the
-// Gaussians, so its k-th derivative is of order sigma^-k: with h <= sigma /
-// RTAB_PER_SIGMA degree 7 leaves less than an ulp of float64 and degree 4 about
-// 3e-10 of the factor, which the float32 staging then rounds at 6e-8.
-//   float64 records: (B, Bh) coefficients of t^0..t^7 as 8 pairs;
-//   float32 records: (B, Bh) of t^0 in float64, of t^1..t^4 as float32 pairs
-//   (the sum of the higher terms is at most h/2 |dB/dr|, a few percent of B).
+// 2 (r / h - k) - 1 on interval k.  Every B_nl and Bh_nl is a function smoothed
+// by the Gaussians, so its j-th derivative is of order sigma^-j.
+//
+// Nothing but the factors themselves is rounded on the way to the records: h is
+// a power of two, so that r / h, k and t are exact; the points are rounded to
+// 2^-36 of an interval, so that their distances are exact as well; the values'
+// transformation to monomial coefficients runs in double-double; and t takes
+// the rounding error of r = sqrt(r^2).  (Coefficients formed in float64 at
+// rounded points lost 20 to 100 ulp: the transformation's rows sum to over 100,
+// and r / h amplifies a rounded r by the number of the interval.)
+//
+//   float64 records, h <= sigma / 20, degree 7: (B, Bh) coefficients of t^0..t^7
+//   as 8 pairs.  Against 64-bit-mantissa arithmetic, relative to the largest
+//   value on the interval: rms 8e-17 beyond the error of the points' values;
+//   with the quadrature's values 2e-16 in the median, where the quadrature
+//   itself has 3e-16 (sums of 64 terms; n_max 8, l_max 6).
+//   float32 records, h <= sigma / 20, degree 4: t^0 as a float64 pair, t^1..t^4
+//   as float32 pairs.
 // (3000-atom water, n_max 8, l_max 6: the quadrature's 64 nodes per edge took
-// 443 us.)
+// 435 us.)
 // ---------------------------------------------------------------------------
 template <typename ST> struct RadRecord;
 template <> struct RadRecord<double> {
     static constexpr int D = 7;
+    static constexpr double PER_SIGMA = 20.0; // intervals per sigma, at least
     double c[D + 1][2];
 };
 template <> struct RadRecord<float> {
     static constexpr int D = 4;
-    double c0[2];
-    float c[D][2];
+    static constexpr double PER_SIGMA = 20.0;
+    static constexpr int ND = 1; // float64 coefficients
+    double c[ND][2];
+    float f[D + 1 - ND][2];
 };
+// In memory a record is NC chunks of 16 bytes, chunk c of an interval's records
+// together: [interval][chunk][n lw], so that the lanes of a wave, which take
+// consecutive factors of an edge, load consecutive chunks.
+template <typename ST> constexpr int rad_chunks() { return sizeof(RadRecord<ST>) / 16; }
+template <typename ST>
+__device__ __forceinline__ RadRecord<ST> rad_load(const double2 *__restrict__ tab, int per, int64_t interval, int t) {
+    double2 w[rad_chunks<ST>()];
+    const double2 *p = tab + interval * (rad_chunks<ST>() * per) + t;
+#pragma unroll
+    for (int c = 0; c < rad_chunks<ST>(); ++c) w[c] = p[c * per];
+    RadRecord<ST> q;
+    __builtin_memcpy(&q, w, sizeof q);
+    return q;
+}
+template <typename ST>
+__device__ __forceinline__ void rad_store(const RadRecord<ST> &q, double2 *__restrict__ tab, int per, int64_t interval,
+                                          int t) {
+    double2 w[rad_chunks<ST>()];
+    __builtin_memcpy(w, &q, sizeof q);
+    for (int c = 0; c < rad_chunks<ST>(); ++c) tab[(interval * rad_chunks<ST>() + c) * per + t] = w[c];
+}
 __device__ __forceinline__ void rad_eval(const RadRecord<double> &q, double t, double &b, double &h) {
     b = q.c[7][0];
     h = q.c[7][1];
@@ -264,54 +299,58 @@ __device__ __forceinline__ void rad_eval(const RadRecord<double> &q, double t, d
 }
 __device__ __forceinline__ void rad_eval(const RadRecord<float> &q, double t, double &b, double &h) {
     const float tf = (float)t;
-    float x = q.c[3][0], y = q.c[3][1];
+    float x = q.f[3][0], y = q.f[3][1];
 #pragma unroll
     for (int k = 2; k >= 0; --k) {
-        x = __builtin_fmaf(x, tf, q.c[k][0]);
-        y = __builtin_fmaf(y, tf, q.c[k][1]);
+        x = __builtin_fmaf(x, tf, q.f[k][0]);
+        y = __builtin_fmaf(y, tf, q.f[k][1]);
     }
-    b = __builtin_fma((double)x, t, q.c0[0]);
-    h = __builtin_fma((double)y, t, q.c0[1]);
+    b = __builtin_fma((double)x, t, q.c[0][0]);
+    h = __builtin_fma((double)y, t, q.c[0][1]);
+}
+
+// one record's coefficients from the values at its interval's D + 1 points
+// (value p at v[p stride]); inv [k][p] (value, remainder): the points' values to
+// the coefficient of t^k
+template <int D>
+__host__ __device__ __forceinline__ void rad_coefficients(const double *v, int64_t stride, const double *inv, double *c,
+                                                          int cstride) {
+    for (int k = 0; k <= D; ++k) {
+        dd s{0.0, 0.0};
+        for (int p = 0; p <= D; ++p) {
+            const double *w = inv + 2 * (k * (D + 1) + p);
+            s = dd_add(s, dd_mul(dd{w[0], w[1]}, dd{v[p * stride], 0.0}));
+        }
+        c[k * cstride] = s.hi;
+    }
 }
 
 // the records from the factors at the intervals' points, vals [interval][point
-// 0..D][n lw] (B, Bh); inv [k][point]: the points' values to the coefficient of t^k
+// 0..D][n lw] (B, Bh)
 template <typename ST>
 __global__ __launch_bounds__(256) void k_radial_records(int64_t count, int per, const double2 *__restrict__ vals,
                                                         const double *__restrict__ inv,
-                                                        RadRecord<ST> *__restrict__ out) {
+                                                        double2 *__restrict__ out) {
     constexpr int D = RadRecord<ST>::D;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) {
         const int64_t iv = i / per;
-        const double2 *v = vals + iv * (D + 1) * per + (i - iv * per);
-        double b[D + 1], h[D + 1];
-#pragma unroll
-        for (int k = 0; k <= D; ++k) {
-            b[k] = h[k] = 0.0;
-#pragma unroll
-            for (int p = 0; p <= D; ++p) {
-                const double2 f = v[(int64_t)p * per];
-                b[k] += inv[k * (D + 1) + p] * f.x;
-                h[k] += inv[k * (D + 1) + p] * f.y;
-            }
-        }
+        const double *v = (const double *)(vals + iv * (D + 1) * per + (i - iv * per));
+        double c[D + 1][2];
+        rad_coefficients<D>(v, 2 * (int64_t)per, inv, &c[0][0], 2);
+        rad_coefficients<D>(v + 1, 2 * (int64_t)per, inv, &c[0][1], 2);
         RadRecord<ST> q;
         if constexpr (sizeof(ST) == 8) {
-#pragma unroll
-            for (int k = 0; k <= D; ++k) {
-                q.c[k][0] = b[k];
-                q.c[k][1] = h[k];
-            }
+            for (int k = 0; k <= D; ++k)
+                for (int j = 0; j < 2; ++j) q.c[k][j] = c[k][j];
         } else {
-            q.c0[0] = b[0];
-            q.c0[1] = h[0];
-#pragma unroll
-            for (int k = 1; k <= D; ++k) {
-                q.c[k - 1][0] = (float)b[k];
-                q.c[k - 1][1] = (float)h[k];
-            }
+            constexpr int ND = RadRecord<ST>::ND;
+            for (int k = 0; k <= D; ++k)
+                for (int j = 0; j < 2; ++j) {
+                    if (k < ND) q.c[k][j] = c[k][j];
+                    else q.f[k - ND][j] = (float)c[k][j];
+                }
         }
-        out[i] = q;
+        rad_store(q, out, per, iv, (int)(i - iv * per));
     }
 }
 
@@ -327,7 +366,7 @@ __global__ __launch_bounds__(BSR) void k_radial_table(Params P, Rows R, const Po
     __shared__ int iv[RAD_TAB_EB]; // -1 - interval for an edge of length 0
     const int tid = threadIdx.x, lw = P.lmax + 1, per = P.n * lw;
     const int64_t origin = *P.rad_origin;
-    const RadRecord<ST> *tab = (const RadRecord<ST> *)P.rtab;
+    const double2 *tab = (const double2 *)P.rtab;
     const float inv_per = 1.0f / (float)per, inv_lw = 1.0f / (float)lw;
     for (int64_t c0 = (int64_t)blockIdx.x * cb; c0 < R.nc; c0 += (int64_t)gridDim.x * cb) {
         const int ncb = (int)((R.nc - c0) < cb ? (R.nc - c0) : cb);
@@ -338,10 +377,13 @@ __global__ __launch_bounds__(BSR) void k_radial_table(Params P, Rows R, const Po
             const int nE = (int)((rp[ncb] - eb) < RAD_TAB_EB ? (rp[ncb] - eb) : RAD_TAB_EB);
             if (eb != rp[0]) __syncthreads(); // the previous pass's readers
             for (int t = tid; t < nE; t += BSR) {
-                const double r = sqrt(edge_r2(R, pos, rp, c0, ncb, eb + t)), x = r * P.rtab_inv_h;
+                const double r2 = edge_r2(R, pos, rp, c0, ncb, eb + t), r = sqrt(r2);
+                const double x = r * P.rtab_inv_h; // exact
                 int k = (int)x; // r < r_cut; the last interval takes the rounding
                 k = k < P.rtab_k ? k : P.rtab_k - 1;
-                tt[t] = 2.0 * (x - (double)k) - 1.0;
+                // sqrt(r2) = r + (r2 - r^2) / (2 r)
+                const double dr2 = r > 0.0 ? __builtin_fma(-r, r, r2) / r : 0.0;
+                tt[t] = __builtin_fma(dr2, P.rtab_inv_h, 2.0 * (x - (double)k) - 1.0);
                 iv[t] = r == 0.0 ? -1 - k : k;
             }
             __syncthreads();
@@ -349,7 +391,7 @@ __global__ __launch_bounds__(BSR) void k_radial_table(Params P, Rows R, const Po
                 const int e = qdiv(k0, inv_per), t = k0 - e * per;
                 const int q = iv[e], k = q < 0 ? -1 - q : q;
                 double b, h;
-                rad_eval(tab[(int64_t)k * per + t], tt[e], b, h);
+                rad_eval(rad_load<ST>(tab, per, k, t), tt[e], b, h);
                 if (q < 0) {
                     b = t - qdiv(t, inv_lw) * lw == 0 ? b : 0.0;
                     h = 0.0;
@@ -532,30 +574,28 @@ hipError_t launch_radial(const Params &P, const Rows &R, const void *pos, bool f
     return launch_radial_from(P, R, pos, f64, ar64, degree, false, st);
 }
 
-constexpr double RTAB_PER_SIGMA = 20.0; // intervals per sigma
 constexpr int RTAB_MAX_K = 4096;
+double radial_table_inv_h(const Params &P, bool st64) {
+    const double h = P.sigma / (st64 ? RadRecord<double>::PER_SIGMA : RadRecord<float>::PER_SIGMA);
+    return std::exp2(-std::floor(std::log2(h)));
+}
 int radial_table_intervals(const Params &P, bool st64) {
     // the Laplace form is singular at r = 0; for GTO (rbf 0) the float64 records
     // (128 bytes a factor) cost more than the exponentials, the float32 ones less
     if (P.rbf == 2 || (P.rbf == 0 && st64)) return 0;
-    const double k = std::ceil(P.rc / P.sigma * RTAB_PER_SIGMA);
+    const double k = std::ceil(P.rc * radial_table_inv_h(P, st64));
     return k <= RTAB_MAX_K ? std::max(1, (int)k) : 0;
 }
 size_t radial_table_bytes(const Params &P, bool st64) {
     const size_t rec = st64 ? sizeof(RadRecord<double>) : sizeof(RadRecord<float>);
     return rec * (size_t)radial_table_intervals(P, st64) * P.n * (P.lmax + 1);
 }
-// The table's values come from the float64 kernels above, over a "structure"
-// whose neighbours sit at the intervals' points, RTAB_ROW of them per row of
-// one center atom (GTO: compensated).
-constexpr int RTAB_ROW = 8;
-hipError_t build_radial_table(const Params &P, bool st64, void *tab) {
-    const int K = radial_table_intervals(P, st64), D = st64 ? RadRecord<double>::D : RadRecord<float>::D, np = D + 1;
-    const int per = P.n * (P.lmax + 1), pts = K * np;
-    // Chebyshev points, and their values to monomial coefficients: the inverse
-    // Vandermonde matrix by Gauss-Jordan elimination in extended precision
-    std::vector<long double> x(np), M((size_t)np * 2 * np, 0.0L);
-    for (int p = 0; p < np; ++p) x[p] = -cosl(M_PIl * (2 * p + 1) / (2 * np));
+// The points x[0..D] of an interval [-1, 1], and the pairs inv [k][p]: the inverse
+// of their Vandermonde matrix by Gauss-Jordan elimination in extended precision.
+static void radial_points(int D, long double *x, double *inv) {
+    const int np = D + 1;
+    std::vector<long double> M((size_t)np * 2 * np, 0.0L);
+    for (int p = 0; p < np; ++p) x[p] = ldexpl(rintl(ldexpl(-cosl(M_PIl * (2 * p + 1) / (2 * np)), 36)), -36);
     for (int p = 0; p < np; ++p) {
         long double v = 1.0L;
         for (int k = 0; k < np; ++k, v *= x[p]) M[(size_t)p * 2 * np + k] = v;
@@ -574,15 +614,32 @@ hipError_t build_radial_table(const Params &P, bool st64, void *tab) {
             for (int k = 0; k < 2 * np; ++k) M[(size_t)r * 2 * np + k] -= f * M[(size_t)c * 2 * np + k];
         }
     }
+    for (int k = 0; k < np; ++k)
+        for (int p = 0; p < np; ++p) {
+            const long double v = M[(size_t)k * 2 * np + np + p];
+            inv[2 * (k * np + p)] = (double)v;
+            inv[2 * (k * np + p) + 1] = (double)(v - (long double)(double)v);
+        }
+}
+
+// The table's values come from the float64 kernels above, over a "structure"
+// whose neighbours sit at the intervals' points, RTAB_ROW of them per row of
+// one center atom (GTO: compensated).
+constexpr int RTAB_ROW = 8;
+hipError_t build_radial_table(const Params &P, bool st64, void *tab) {
+    const int K = radial_table_intervals(P, st64), D = st64 ? RadRecord<double>::D : RadRecord<float>::D, np = D + 1;
+    const int per = P.n * (P.lmax + 1), pts = K * np;
+    const long double h = 1.0L / (long double)radial_table_inv_h(P, st64);
+    std::vector<long double> x(np);
     // one upload: inv [k][p], positions of the center (0) and the points, row
     // offsets, columns; then the values
-    std::vector<double> up((size_t)np * np + 3 * ((size_t)pts + 1), 0.0);
-    for (int k = 0; k < np; ++k)
-        for (int p = 0; p < np; ++p) up[(size_t)k * np + p] = (double)M[(size_t)k * 2 * np + np + p];
-    double *pos = up.data() + (size_t)np * np;
+    const size_t o_pos = 2 * (size_t)np * np;
+    std::vector<double> up(o_pos + 3 * ((size_t)pts + 1), 0.0);
+    radial_points(D, x.data(), up.data());
+    double *pos = up.data() + o_pos;
     for (int k = 0; k < K; ++k)
-        for (int p = 0; p < np; ++p)
-            pos[3 * ((size_t)k * np + p + 1)] = (double)(((long double)k + (x[p] + 1.0L) / 2.0L) / K * (long double)P.rc);
+        for (int p = 0; p < np; ++p) // exact: 12 bits of k, 37 of the point
+            pos[3 * ((size_t)k * np + p + 1)] = (double)(((long double)k + (x[p] + 1.0L) / 2.0L) * h);
     const int nrow = (pts + RTAB_ROW - 1) / RTAB_ROW;
     const size_t o_row = up.size();
     up.resize(o_row + nrow + 1 + ((size_t)pts + nrow + 1) / 2, 0.0);
@@ -608,21 +665,31 @@ hipError_t build_radial_table(const Params &P, bool st64, void *tab) {
         R.row_ptr = R.e_origin = Pp.rad_origin;
         R.cols = reinterpret_cast<const int32_t *>(dev + o_row + nrow + 1);
         R.centers = R.cols + pts;
-        e = launch_radial_from(Pp, R, dev + (size_t)np * np, true, false, (double)RTAB_ROW, true, 0);
+        e = launch_radial_from(Pp, R, dev + o_pos, true, false, (double)RTAB_ROW, true, 0);
     }
     if (e == hipSuccess) {
         const int64_t count = (int64_t)K * per;
         const unsigned blocks = (unsigned)std::min<int64_t>((count + 255) / 256, 4096);
         if (st64)
             hipLaunchKernelGGL(k_radial_records<double>, dim3(blocks), dim3(256), 0, 0, count, per, vals, dev,
-                               (RadRecord<double> *)tab);
+                               (double2 *)tab);
         else
             hipLaunchKernelGGL(k_radial_records<float>, dim3(blocks), dim3(256), 0, 0, count, per, vals, dev,
-                               (RadRecord<float> *)tab);
+                               (double2 *)tab);
         e = hipGetLastError();
     }
     const hipError_t f = hipFree(dev); // waits for the kernels
     return e == hipSuccess ? f : e;
+}
+
+// the float64 records' arithmetic on the host: the points, and the coefficients of values there
+extern "C" void soap_radial_record64(const double *vals, double *points, double *coef) {
+    constexpr int D = RadRecord<double>::D;
+    long double x[D + 1];
+    double inv[2 * (D + 1) * (D + 1)];
+    radial_points(D, x, inv);
+    for (int p = 0; p <= D; ++p) points[p] = (double)x[p];
+    rad_coefficients<D>(vals, 1, inv, coef, 1);
 }
 
 // dynamic LDS above the default limit for every variant (set_lds_limits)

@@ -121,17 +121,17 @@ __device__ __forceinline__ cdptr as_const(const double *p) { return (cdptr)p; }
 struct dd {
     double hi, lo;
 };
-__device__ __forceinline__ dd dd_fast_sum(double a, double b) { // |a| >= |b|
+__host__ __device__ __forceinline__ dd dd_fast_sum(double a, double b) { // |a| >= |b|
 #pragma clang fp contract(off)
     const double s = a + b;
     return dd{s, b - (s - a)};
 }
-__device__ __forceinline__ dd dd_two_sum(double a, double b) {
+__host__ __device__ __forceinline__ dd dd_two_sum(double a, double b) {
 #pragma clang fp contract(off)
     const double s = a + b, bb = s - a;
     return dd{s, (a - (s - bb)) + (b - bb)};
 }
-__device__ __forceinline__ dd dd_add(dd a, dd b) {
+__host__ __device__ __forceinline__ dd dd_add(dd a, dd b) {
 #pragma clang fp contract(off)
     dd s = dd_two_sum(a.hi, b.hi);
     const dd t = dd_two_sum(a.lo, b.lo);
@@ -140,7 +140,7 @@ __device__ __forceinline__ dd dd_add(dd a, dd b) {
     s.lo += t.lo;
     return dd_fast_sum(s.hi, s.lo);
 }
-__device__ __forceinline__ dd dd_mul(dd a, dd b) {
+__host__ __device__ __forceinline__ dd dd_mul(dd a, dd b) {
 #pragma clang fp contract(off)
     const double p = a.hi * b.hi;
     double e = fma(a.hi, b.hi, -p);

@@ -35,9 +35,9 @@ struct Params {
                                // edge of length 0 has its B_n0 and zeros
     int64_t rad_stride;        // bytes per edge
     const int64_t *rad_origin; // row offset of the range's first center
-    const void *rtab;          // table of the radial factors (radial.hip; NULL: none), records [interval][n][l]
-    int rtab_k;                // intervals on [0, r_cut]
-    double rtab_inv_h;         // intervals per length
+    const void *rtab;          // table of the radial factors (radial.hip; NULL: none)
+    int rtab_k;                // intervals on [0, r_cut], the last one possibly beyond
+    double rtab_inv_h;         // intervals per length, a power of two
     const double *c0;          // on-site term [n]
     const double *e2t;         // GTO: [64][2] 2^(j/64) as (value, remainder) (soap_exp2_table64)
     const double *Nt;          // [lmax+2][lmax+2] N_lm (2m-1)!! / (l-m)! (division-free recurrence)
@@ -250,6 +250,7 @@ hipError_t launch_radial(const Params &P, const Rows &R, const void *pos, bool f
                          hipStream_t st);
 // the table of the radial factors (0 intervals: the basis has none)
 int radial_table_intervals(const Params &P, bool st64);
+double radial_table_inv_h(const Params &P, bool st64);
 size_t radial_table_bytes(const Params &P, bool st64);
 hipError_t build_radial_table(const Params &P, bool st64, void *tab);
 hipError_t radial_set_lds_limit(int lim);

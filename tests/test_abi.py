@@ -55,6 +55,38 @@ def test_host_exp2_table(lib):
             assert abs((mp.mpf(t[2 * j]) + mp.mpf(t[2 * j + 1]) - v) / v) < mp.mpf(2) ** -104, j
 
 
+def test_host_radial_record(lib):
+    """The float64 records of the radial table on functions smoothed by a Gaussian
+    of width sigma, intervals of sigma / 20, from values rounded to float64.  The
+    bound is 2.3 ulp of the function's largest value: half an ulp of the values
+    times the Lebesgue constant 2.3 of the points, half an ulp of the constant
+    coefficient and of the last operation of Horner's scheme, a tenth for the
+    others (truncation is below a hundredth)."""
+    f = lib.soap_radial_record64
+    f.argtypes = [ctypes.c_void_p] * 3
+    f.restype = None
+    vals, pts, coef = np.zeros(8), np.empty(8), np.empty(8)
+    f(vals.ctypes.data, pts.ctypes.data, coef.ctypes.data)
+    assert np.all(coef == 0) and np.all(pts * 2.0 ** 36 == np.rint(pts * 2.0 ** 36)) and np.all(np.diff(pts) > 0)
+    h = 1.0 / 64  # sigma 0.3125 and more
+    s = mp.mpf("0.32")
+    shapes = [lambda r: mp.mpf(1), lambda r: mp.exp(-(r - 2) ** 2 / (2 * s * s)), lambda r: mp.sin(r / s),
+              lambda r: (r - 2) / s * mp.exp(-(r - 2) ** 2 / (2 * s * s))]
+    with mp.workdps(40):
+        for fn in shapes:
+            for k in (0, 3, 107, 128, 200, 383):
+                r = lambda t: (k + (t + 1) / 2) * mp.mpf(h)
+                vals = np.array([float(fn(r(mp.mpf(p)))) for p in pts])
+                f(vals.ctypes.data, pts.ctypes.data, coef.ctypes.data)
+                ts = np.linspace(-1, 1, 33)
+                exact = [fn(r(mp.mpf(t))) for t in ts]
+                b = np.full(33, coef[7])
+                for j in range(6, -1, -1):  # fused, as in the kernel
+                    b = np.array([float(mp.mpf(x) * mp.mpf(t) + mp.mpf(coef[j])) for x, t in zip(b, ts)])
+                err = max(abs(mp.mpf(x) - e) for x, e in zip(b, exact))
+                assert err < 2.3 * 2.0 ** -53, (k, err)  # an ulp below 1
+
+
 @pytest.mark.parametrize("r_cut,n_max,l_max,sigma", [(5.0, 4, 4, 0.5), (6.0, 8, 6, 0.5), (6.0, 12, 12, 0.5),
                                                      (6.0, 1, 2, 0.4)])
 def test_host_gto_constants_match_oracle(lib, r_cut, n_max, l_max, sigma):

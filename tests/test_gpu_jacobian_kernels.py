@@ -130,6 +130,43 @@ def test_density_step_matrix_and_shared(n, l, dtype, arith):
         assert torch.all(err <= TOL[dtype] * scale)
 
 
+def _dimers(n_pairs, r_cut):
+    """Pairs of atoms far apart, in random directions at distances over (0, r_cut)."""
+    rng = np.random.default_rng(1)
+    pos = np.zeros((2 * n_pairs, 3))
+    pos[:, 1] = np.repeat(20.0 * np.arange(n_pairs), 2)
+    v = rng.standard_normal((n_pairs, 3))
+    pos[1::2] += v / np.linalg.norm(v, axis=1)[:, None] * rng.uniform(0.3, 0.98 * r_cut, n_pairs)[:, None]
+    return workloads.Structure(pos.astype(np.float32), np.tile([1, 8], n_pairs).astype(np.int32), 0.0, 0)
+
+
+@pytest.mark.parametrize("rbf,n,l,bound_c,bound_j", [("polynomial", 8, 6, 3.3e-15, 1.9e-15),
+                                                     ("polynomial", 4, 3, 1.3e-15, 1.4e-15),
+                                                     ("gto", 10, 4, None, 7.1e-16)])
+def test_float64_table_keeps_the_direct_evaluations_bits(rbf, n, l, bound_c, bound_j):
+    """Float64 dimers through the radial table: the root mean square errors of the
+    coefficients (the polynomial's; GTO coefficients don't use the table) and of
+    the center blocks are no larger than with every factor evaluated from its
+    definition (the bounds: measured so, against the same oracle in long double)."""
+    st = _dimers(400, 6.0)
+    wl = _wl((1, 8), rbf, n, l, r_cut=6.0)
+    print(f"[kernels] table {wl.name}", flush=True)
+    g = gpu_run(wl, st, "float64", coefficients=True)
+    ref = oracle.OracleSOAP(wl.species, wl.r_cut, n, l, wl.sigma, rbf).compute(
+        st.pos64, st.Z, centers=np.arange(800), jacobian=True, coefficients=True)
+    k, o = np.arange(800), np.tile([1, 0], 400)  # the neighbour's species
+    c, cr = (a.reshape(800, 2, n, -1)[k, o] for a in (g["c"], ref["c"]))
+    ec = np.abs(c - cr).max(-1) / np.abs(cr).max(-1)  # per center and radial index
+    ej = []
+    for i in range(800):
+        b = [b for b in range(ref["blk_ptr"][i], ref["blk_ptr"][i + 1]) if ref["blk_j"][b] == i][0]
+        ej.append(np.abs(g["jself"][i] - ref["jac"][b]).max() / np.abs(ref["jac"][b]).max())
+    rc, rj = np.sqrt(np.mean(ec ** 2)), np.sqrt(np.mean(np.square(ej)))
+    print(f"[kernels] table {wl.name}: coefficients {rc:.2e}, center blocks {rj:.2e}", flush=True)
+    assert bound_c is None or rc < bound_c
+    assert rj < bound_j
+
+
 @pytest.mark.parametrize("n,l,tile", [(4, 5, 3), (5, 5, 3), (8, 3, 3), (3, 6, 3), (2, 2, 4), (8, 6, 2)])
 def test_float64_tile_plan(n, l, tile):
     """The float64 edge Jacobian kernel takes the widest tile that keeps three
