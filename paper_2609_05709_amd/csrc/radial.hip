@@ -249,8 +249,11 @@ __global__ __launch_bounds__(BSR) void k_radial_flat(Params P, Rows R, const Pos
 //   value on the interval: rms 8e-17 beyond the error of the points' values;
 //   with the quadrature's values 2e-16 in the median, where the quadrature
 //   itself has 3e-16 (sums of 64 terms; n_max 8, l_max 6).
-//   float32 records, h <= sigma / 20, degree 4: t^0 as a float64 pair, t^1..t^4
-//   as float32 pairs.
+//   float32 records, h <= sigma / 16, degree 6: t^0..t^2 as float64 pairs, t^3..t^6 as
+//   float32 pairs.  The factor before its one rounding to float32 is off by 1e-12 to
+//   4e-12 of the interval's largest value, the stored factor by the same 2.53e-8 rms
+//   as that of the direct evaluation.  (Degree 4 with float32 from t^1 on, 48 bytes:
+//   2e-9 and 5e-8 to 1e-6, worst next to a factor's zeros.)
 // (3000-atom water, n_max 8, l_max 6: the quadrature's 64 nodes per edge took
 // 435 us.)
 // ---------------------------------------------------------------------------
@@ -261,9 +264,9 @@ template <> struct RadRecord<double> {
     double c[D + 1][2];
 };
 template <> struct RadRecord<float> {
-    static constexpr int D = 4;
-    static constexpr double PER_SIGMA = 20.0;
-    static constexpr int ND = 1; // float64 coefficients
+    static constexpr int D = 6;
+    static constexpr double PER_SIGMA = 16.0;
+    static constexpr int ND = 3; // float64 coefficients
     double c[ND][2];
     float f[D + 1 - ND][2];
 };
@@ -305,8 +308,13 @@ __device__ __forceinline__ void rad_eval(const RadRecord<float> &q, double t, do
         x = __builtin_fmaf(x, tf, q.f[k][0]);
         y = __builtin_fmaf(y, tf, q.f[k][1]);
     }
-    b = __builtin_fma((double)x, t, q.c[0][0]);
-    h = __builtin_fma((double)y, t, q.c[0][1]);
+    b = (double)x;
+    h = (double)y;
+#pragma unroll
+    for (int k = 2; k >= 0; --k) {
+        b = __builtin_fma(b, t, q.c[k][0]);
+        h = __builtin_fma(h, t, q.c[k][1]);
+    }
 }
 
 // one record's coefficients from the values at its interval's D + 1 points
