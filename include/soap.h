@@ -179,6 +179,10 @@ int soap_create(const int32_t *species_Z, int32_t n_species, double r_cut, int32
  *              step;
  *   "pipeline_density_wg": 0..16 (default 0 = no cap), workgroups per
  *              CU of the density kernel while pipelined.
+ * "dtype", "arith" and the kernel choices may build the radial factors' table of the
+ * new arithmetic (device memory, once per context and arithmetic); calls already
+ * queued, and graphs captured over earlier calls, keep theirs.  "quad_n" changes the
+ * constants in place and first waits for the device.
  * Options take effect for calls made after this one; changing "dtype"
  * discards the neighbour list.  Errors: SOAP_EINVAL.
  */

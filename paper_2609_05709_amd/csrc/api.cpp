@@ -98,8 +98,11 @@ struct soap_ctx {
     NbrWork nw{};
     DevBuf b_zero, b_bstart, b_acell, b_srec, b_sspec, b_deg, b_slots, b_scan, b_spec, b_row, b_cols, b_cscratch;
     DevBuf b_avg, b_avg_part; // averaged modes: per-center rows, column partial sums and means
-    DevBuf b_rtab;            // table of the radial factors
-    int rtab_kind = 0;        // what it holds: 0 nothing, 4 / 8 float32 / float64 records
+    // tables of the radial factors, float32 and float64 records: each built once
+    // and left alone (queued calls and captured graphs read it), until quad_n
+    // changes the constants
+    DevBuf b_rtab[2];
+    bool rtab_built[2] = {false, false};
     DevBuf b_radial;          // radial factors of a call's edges, where they don't go to its edge blocks
     std::vector<int64_t> h_row; // polynomial quadrature: host copy of the CSR row offsets
     // periodic cell (soap_set_cell) and the extended structure of the last build
@@ -446,15 +449,14 @@ int plan_launches(soap_ctx *c) {
     P.rtab = nullptr;
     P.rtab_k = radial_table_intervals(P, st64);
     if (P.rtab_k > 0 && (reads_radial(c, 0) || reads_radial(c, 1))) {
-        const int kind = st64 ? 8 : 4;
-        if (c->rtab_kind != kind) {
-            c->rtab_kind = 0;
-            hipError_t e = c->b_rtab.ensure(radial_table_bytes(P, st64));
-            if (e == hipSuccess) e = build_radial_table(P, st64, c->b_rtab.p);
+        DevBuf &tab = c->b_rtab[st64];
+        if (!c->rtab_built[st64]) {
+            hipError_t e = tab.ensure(radial_table_bytes(P, st64));
+            if (e == hipSuccess) e = build_radial_table(P, st64, tab.p);
             if (e != hipSuccess) return hip_fail(c, e, "radial table");
-            c->rtab_kind = kind;
+            c->rtab_built[st64] = true;
         }
-        P.rtab = c->b_rtab.p;
+        P.rtab = tab.p;
         P.rtab_inv_h = radial_table_inv_h(P, st64);
     }
     return SOAP_OK;
@@ -677,7 +679,7 @@ int upload_constants(soap_ctx *c) {
     P.dti = reinterpret_cast<const uint16_t *>(d + o_di);
     P.dtab = c->d_dtab.as<uint32_t>();
     P.tri_lw = (int)c->dtab.size();
-    c->rtab_kind = 0; // of the previous constants
+    c->rtab_built[0] = c->rtab_built[1] = false; // of the previous constants
     return plan_launches(c);
 }
 
@@ -709,6 +711,19 @@ struct SegTimer {
         if (b && hipEventRecord(b, st) == hipSuccess) c->recs.push_back({seg, a, b});
         else c->pool.push_back(a);
         a = nullptr;
+    }
+};
+
+// the context's device as the current one: what an option allocates or builds is
+// the context's, whichever device the calling thread has current
+struct DeviceScope {
+    int caller = -1;
+    explicit DeviceScope(int device) {
+        int d = -1;
+        if (hipGetDevice(&d) == hipSuccess && d != device && hipSetDevice(device) == hipSuccess) caller = d;
+    }
+    ~DeviceScope() {
+        if (caller >= 0) (void)hipSetDevice(caller);
     }
 };
 
@@ -857,6 +872,7 @@ int soap_create(const int32_t *species_Z, int32_t n_species, double r_cut, int32
 
 int soap_set_option(soap_ctx *c, const char *key, int64_t value) {
     if (!c || !key) return SOAP_EINVAL;
+    DeviceScope on(c->device);
     if (!std::strcmp(key, "dtype")) {
         if (value != SOAP_FP32 && value != SOAP_FP64) return fail(c, SOAP_EINVAL, "dtype must be SOAP_FP32 or SOAP_FP64");
         if (value == c->dtype) return SOAP_OK;
@@ -923,6 +939,9 @@ int soap_set_option(soap_ctx *c, const char *key, int64_t value) {
     if (!std::strcmp(key, "quad_n")) {
         if (value < 8 || value > 256) return fail(c, SOAP_EINVAL, "quad_n must be in 8..256");
         if ((int)value == c->Q) return SOAP_OK;
+        // calls still queued, on any stream, read the constants that change
+        const hipError_t e = hipDeviceSynchronize();
+        if (e != hipSuccess) return hip_fail(c, e, "quad_n (sync)");
         c->Q = (int)value;
         return upload_constants(c);
     }
@@ -1703,7 +1722,7 @@ void soap_destroy(soap_ctx *c) {
     (void)hipDeviceSynchronize();
     for (DevBuf *b : {&c->d_const, &c->d_dtab, &c->d_fmap, &c->d_lut, &c->b_zero, &c->b_bstart, &c->b_acell,
                       &c->b_srec, &c->b_sspec, &c->b_deg, &c->b_slots, &c->b_scan, &c->b_spec, &c->b_row, &c->b_cols,
-                      &c->b_cscratch, &c->b_radial, &c->b_rtab, &c->b_avg, &c->b_avg_part, &c->b_img_lohi, &c->b_img_cnt, &c->b_img_start,
+                      &c->b_cscratch, &c->b_radial, &c->b_rtab[0], &c->b_rtab[1], &c->b_avg, &c->b_avg_part, &c->b_img_lohi, &c->b_img_cnt, &c->b_img_start,
                       &c->b_pos_ext, &c->b_Z_ext, &c->b_map_atom, &c->b_map_img, &c->b_iota})
         b->release();
     if (c->h_flags) (void)hipHostFree(c->h_flags);

@@ -194,3 +194,78 @@ def test_float64_tile_plan(n, l, tile):
     sp = Soap((1, 8), 5.5, n, l, 0.5, "gto", dtype="float64")
     assert (sp.get_option("jacobian_kernel"), sp.get_option("jacobian_tile")) == (0, tile)
     sp.close()
+
+
+def _table_context(arith):
+    """A small polynomial structure with its neighbour rows, and the outputs of both arithmetics."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    st = workloads.random_small(60, 4, 4.5, species=(1, 8), dmin=0.9)
+    pos, Z = torch.from_numpy(st.pos).cuda(), torch.from_numpy(st.Z).cuda()
+    ref = []
+    for a in ("mixed", "fp64"):
+        sp = Soap((1, 8), 5.0, 6, 5, 0.5, "polynomial", arith=a)
+        sp.build_neighbors(pos, Z)
+        ref.append([t.clone() for t in sp.derivatives()])
+        sp.close()
+    assert not torch.equal(ref[0][1], ref[1][1])
+    sp = Soap((1, 8), 5.0, 6, 5, 0.5, "polynomial", arith=arith)
+    sp.build_neighbors(pos, Z)
+    return sp, ref
+
+
+def test_options_leave_queued_calls_alone():
+    """A call queued behind other work on its own stream keeps the arithmetic it
+    was made with, and its radial table, when the option changes before it runs."""
+    import torch
+    sp, ref = _table_context("fp64")
+    busy = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for k in range(3):  # both tables exist from the second pass on
+        print(f"[kernels] queued calls {k}", flush=True)
+        with torch.cuda.stream(side):
+            for _ in range(10):
+                busy = busy @ busy
+                busy /= busy.norm()
+            wide = [t.clone() for t in sp.derivatives()]
+        sp.set_option("arith", 0)
+        with torch.cuda.stream(side):
+            mixed = [t.clone() for t in sp.derivatives()]
+        sp.set_option("arith", 1)
+        side.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(wide, ref[1]))
+        assert all(torch.equal(a, b) for a, b in zip(mixed, ref[0]))
+    sp.close()
+
+
+def test_captured_calls_keep_their_table():
+    """A graph captured over the allocation-free call gives the same outputs after
+    the arithmetic was changed and calls in the other one ran."""
+    import ctypes
+
+    import torch
+    sp, ref = _table_context("mixed")
+    out = [torch.empty_like(t) for t in ref[0]]
+
+    def call():
+        stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert sp._L.soap_derivatives_batch_noalloc(sp._h, 0, sp.n_centers, *(t.data_ptr() for t in out), stream) == 0
+
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for k in range(3):
+        print(f"[kernels] replay {k}", flush=True)
+        sp.set_option("arith", 1)
+        wide = sp.derivatives()
+        assert all(torch.equal(a, b) for a, b in zip(wide, ref[1]))
+        for t in out:
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, ref[0]))
+        sp.set_option("arith", 0)
+    sp.close()
