@@ -778,6 +778,13 @@ size_t block_bytes(const soap_ctx *c) { return (c->dtype == SOAP_FP64 ? 8 : 4) *
 // written (all bases but one radial function of one species in float64
 // arithmetic with float32 outputs)
 bool radial_in_place(const soap_ctx *c) { return block_bytes(c) >= radial_bytes_per_edge(c); }
+// the buffer of the factors of E edges, where their blocks are too short; there
+// before a derivatives call, so that soap_derivatives_batch_noalloc finds it
+int ensure_edge_radial(soap_ctx *c, int64_t E) {
+    if (radial_in_place(c)) return SOAP_OK;
+    const hipError_t e = c->b_radial.ensure(radial_bytes_per_edge(c) * (size_t)E);
+    return e == hipSuccess ? SOAP_OK : hip_fail(c, e, "hipMalloc(radial factors)");
+}
 // most edges that the rows of `count` centers can have
 int64_t edges_bound(const soap_ctx *c, int64_t count) { return std::min(c->E, count * (int64_t)c->maxdeg); }
 
@@ -885,7 +892,8 @@ int soap_set_option(soap_ctx *c, const char *key, int64_t value) {
             return fail(c, SOAP_EINVAL, "arith must be SOAP_ARITH_MIXED or SOAP_ARITH_FP64");
         if (value == c->arith) return SOAP_OK;
         c->arith = (int)value;
-        return plan_launches(c); // staging sizes and occupancy of the kernels
+        const int rc = plan_launches(c); // staging sizes and occupancy of the kernels
+        return rc == SOAP_OK && c->have_rows ? ensure_edge_radial(c, c->E) : rc;
     }
     if (!std::strcmp(key, "batch_centers")) {
         if (value < 0) return fail(c, SOAP_EINVAL, "batch_centers must be >= 0");
@@ -1212,10 +1220,7 @@ int soap_build_neighbors(soap_ctx *c, int64_t n_atoms, const void *pos_dev, cons
     if ((rc = build_rows(c, n_rows_atoms, n_atoms, pos_rows, Z_rows, n_centers, cen_rows, &E, st)) != SOAP_OK)
         return rc;
     timer.done();
-    if (!radial_in_place(c)) {
-        hipError_t e = c->b_radial.ensure(radial_bytes_per_edge(c) * (size_t)E);
-        if (e != hipSuccess) return hip_fail(c, e, "hipMalloc(radial factors)");
-    }
+    if ((rc = ensure_edge_radial(c, E)) != SOAP_OK) return rc;
     c->have_rows = true;
     c->n_atoms = n_atoms;
     c->n_ext = n_rows_atoms;

@@ -269,3 +269,35 @@ def test_captured_calls_keep_their_table():
         assert all(torch.equal(a, b) for a, b in zip(out, ref[0]))
         sp.set_option("arith", 0)
     sp.close()
+
+
+def test_noalloc_call_after_a_change_of_arithmetic():
+    """One species and one radial function: in float64 arithmetic an edge's block
+    cannot hold its factors.  Their buffer is there when the arithmetic changes
+    after the neighbour build: the call can be captured, which an allocation would
+    end with an error."""
+    import ctypes
+
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    st = workloads.random_small(50, 4, 4.0, species=(8,), dmin=0.9)
+    pos, Z = torch.from_numpy(st.pos).cuda(), torch.from_numpy(st.Z).cuda()
+    sp = Soap((8,), 5.0, 1, 4, 0.5, "polynomial", arith="fp64")
+    sp.build_neighbors(pos, Z)
+    ref = [t.clone() for t in sp.derivatives()]
+    sp.close()
+    sp = Soap((8,), 5.0, 1, 4, 0.5, "polynomial")
+    sp.build_neighbors(pos, Z)
+    sp.set_option("arith", 1)
+    out = [torch.full_like(t, float("nan")) for t in ref]
+    torch.cuda.synchronize()
+    print("[kernels] capture after a change of arithmetic", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        rc = sp._L.soap_derivatives_batch_noalloc(sp._h, 0, sp.n_centers, *(t.data_ptr() for t in out), stream)
+    assert rc == 0
+    graph.replay()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, ref))
+    sp.close()
