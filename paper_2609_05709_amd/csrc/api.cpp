@@ -785,8 +785,12 @@ int ensure_edge_radial(soap_ctx *c, int64_t E) {
     const hipError_t e = c->b_radial.ensure(radial_bytes_per_edge(c) * (size_t)E);
     return e == hipSuccess ? SOAP_OK : hip_fail(c, e, "hipMalloc(radial factors)");
 }
-// most edges that the rows of `count` centers can have
-int64_t edges_bound(const soap_ctx *c, int64_t count) { return std::min(c->E, count * (int64_t)c->maxdeg); }
+// edges of centers [first, first + count): their number where the row offsets are
+// on the host (the quadrature), else the most it can be
+int64_t edges_of(const soap_ctx *c, int64_t first, int64_t count) {
+    if (c->h_row.size() == (size_t)c->nc + 1) return c->h_row[first + count] - c->h_row[first];
+    return std::min(c->E, count * (int64_t)c->maxdeg);
+}
 
 // The polynomial quadrature's share of a batch's memory (float64 pairs of
 // every edge), which the batch plan and the limit of
@@ -797,7 +801,7 @@ size_t quad_bytes_per_edge(const soap_ctx *c) {
 }
 size_t quad_bytes(const soap_ctx *c, int64_t first, int64_t count) {
     if (count == 0 || c->h_row.size() != (size_t)c->nc + 1) return 0;
-    return quad_bytes_per_edge(c) * (size_t)(c->h_row[first + count] - c->h_row[first]);
+    return quad_bytes_per_edge(c) * (size_t)edges_of(c, first, count);
 }
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -1077,9 +1081,10 @@ static int build_rows(soap_ctx *c, int64_t n_atoms, int64_t center_bound, const 
     const int64_t cap0 = c->b_cols.p ? (int64_t)(c->b_cols.cap / 4) : 0;
     if (cap0 > 0 && (e = nbr_pack(w, n_centers, row, c->b_cols.as<int32_t>(), cap0, st)) != hipSuccess)
         return hip_fail(c, e, "neighbour rows");
-    // soap_derivatives_batch_noalloc's limit counts the polynomial quadrature's
-    // edges from a host copy of the row offsets: copied with the flags, one
-    // synchronisation.
+    // The polynomial quadrature's buffer of radial factors is sized for a batch's
+    // edges, as soap_plan_batches counts them and the limit of
+    // soap_derivatives_batch_noalloc does: a host copy of the row offsets, copied
+    // with the flags, one synchronisation.
     c->h_row.clear();
     const bool rows_to_host = c->rbf == SOAP_RBF_POLYNOMIAL;
     if (rows_to_host) {
@@ -1321,7 +1326,7 @@ static bool jacobian_path_ok(const soap_ctx *c, int mode) {
 static int prepare_radial(soap_ctx *c, int mode, int64_t first, int64_t count, void *jac_edge, int64_t origin,
                           hipStream_t st) {
     const size_t per = radial_bytes_per_edge(c), block = block_bytes(c);
-    const int64_t n = edges_bound(c, count);
+    const int64_t n = edges_of(c, first, count);
     const bool in_place = mode == 1 && jac_edge && radial_in_place(c);
     c->P.rad = in_place ? jac_edge : nullptr;
     c->P.rad_stride = (int64_t)(in_place ? block : per);

@@ -283,3 +283,33 @@ def test_batch_centers_option(case):
             assert torch.equal(x, y), (case, B)
     sp.set_option("batch_centers", 0)
     sp.close()
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_descriptor_batches_of_uneven_rows_stay_in_the_budget(dtype):
+    """Polynomial descriptor batches keep the radial factors of their own edges
+    only: a batch of nearly isolated centers takes no memory for the long rows of
+    the others."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    rng = np.random.default_rng(3)
+    sparse = np.zeros((2000, 3))
+    sparse[:, 0] = np.repeat(30.0 * np.arange(1, 1001), 2) + np.tile([0.0, 1.5], 1000)
+    clump = rng.uniform(-2.4, 2.4, (500, 3))
+    pos = torch.from_numpy(np.concatenate([sparse, clump])).to("cuda", getattr(torch, dtype))
+    Z = torch.full((2500,), 8, dtype=torch.int32, device="cuda")
+    sp = Soap((8,), 6.0, 8, 6, 0.5, "polynomial", dtype=dtype)
+    E = sp.build_neighbors(pos, Z)
+    assert E > 200000
+    out = torch.empty((2000, sp.n_features), dtype=sp.dtype, device="cuda")
+    budget = 2000 * (sp.n_features * sp.dtype.itemsize + 16 * 8 * 7) + 1024
+    assert sp.plan_batches(budget, jacobian=False)[0][1] == 2000
+    sp.compute_batch(0, 2)  # the kernels' first launch
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    sp.compute_batch(0, 2000, out)
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    print(f"[batches] uneven rows {dtype}: {used} bytes", flush=True)
+    assert used <= budget + (4 << 20)  # the allocator's granularity
+    sp.close()
