@@ -94,7 +94,7 @@ template <typename PosT, typename OutT, typename AT, int HI>
 __global__ __launch_bounds__(64 * EB_MAX_WAVES, 4) void k_edge_blocks(Params P, Rows R, const PosT *__restrict__ pos,
                                                                      int Q, int RB, int split,
                                                                      const AT *__restrict__ c_scratch,
-                                                                     OutT *__restrict__ jedge) {
+                                                                     typename EdgeBlocks<OutT, RBF_BUFFERED>::ptr jedge) {
     using AT2 = typename Pair<AT>::type;
     using AT4 = Quad<AT>;
     constexpr int NCH = HI * (HI + 1) / 2;

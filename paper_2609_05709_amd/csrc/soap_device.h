@@ -2489,13 +2489,23 @@ constexpr int jac_min_waves(int ab, int NT, int LWT) {
     return (ab == 4 && (LWT == 0 || LWT <= 5 || (LWT == 7 && NT <= 8))) ? 3 : 2;
 }
 
+// The edge blocks as an edge Jacobian kernel's parameter: not restrict where they
+// hold the radial pass's factors on entry (P.rad), which are read before they are
+// written over.
+template <typename OutT, int RBF> struct EdgeBlocks {
+    using ptr = OutT *;
+};
+template <typename OutT> struct EdgeBlocks<OutT, 0> {
+    using ptr = OutT *__restrict__;
+};
+
 // AT: precision of the final assembly (OutT, or double for float64
 // arithmetic with float32 outputs).
 // RBF: 0 the GTO factors evaluated in the staging, else the radial pass's
 template <typename PosT, typename OutT, int NT, int LWT, int RBF, typename AT = OutT>
 __global__ __launch_bounds__(BSJ, jac_min_waves(sizeof(AT), NT, LWT)) void k_jacobian(Params P, Rows R, const PosT *__restrict__ pos,
                                                                             int W, int vec, const AT *__restrict__ c_scratch,
-                                                                            OutT *__restrict__ jedge) {
+                                                                            typename EdgeBlocks<OutT, RBF>::ptr jedge) {
     using AT2 = typename Pair<AT>::type;
     constexpr int ab = sizeof(AT);
     // 16-byte aligned: the carved regions are read with 16-byte LDS accesses
