@@ -352,7 +352,6 @@ hipError_t launch_edge_blocks(const Params &P, const Rows &R, const void *pos, b
                               hipStream_t st) {
     if (R.nc <= 0) return hipSuccess;
     Params Pk = P;
-    Rows Rk = R;
     // Few centers: several workgroups per center, each some of its chunks, until
     // about four workgroups per CU (what stays resident) have work (64-water
     // cluster, n_max 4, l_max 4: 41 us with one workgroup per center, 24 with
@@ -362,8 +361,22 @@ hipError_t launch_edge_blocks(const Params &P, const Rows &R, const void *pos, b
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev_id);
     const int64_t want = (4 * (int64_t)ncu) / R.nc, chunks = (int64_t)std::ceil(degree / (4.0 * cfg.Q));
     int Q = cfg.Q, RB = cfg.RB, split = (int)std::max<int64_t>(1, std::min(want, chunks));
-    void *args[] = {&Pk, &Rk, &pos, &Q, &RB, &split, &c_scratch, &jedge};
-    return hipLaunchKernel(eb_kernel(f64, ar64, P.lmax + 1), dim3((unsigned)(R.nc * split)), dim3(cfg.threads), args, cfg.lds, st);
+    // a launch has fewer than 2^32 threads: more centers take several
+    const int64_t most = (int64_t)UINT32_MAX / cfg.threads;
+    const size_t per = (f64 || ar64 ? 8 : 4) * 4 * (size_t)P.S * P.n * P.L; // scratch of a center
+    for (int64_t c0 = 0; c0 < R.nc; c0 += most) {
+        Rows Rk = R;
+        Rk.nc = std::min(most, R.nc - c0);
+        Rk.row_ptr += c0;
+        Rk.c_base += c0;
+        if (Rk.centers) Rk.centers += c0;
+        const void *cs = (const char *)c_scratch + per * (size_t)c0;
+        void *args[] = {&Pk, &Rk, &pos, &Q, &RB, &split, &cs, &jedge};
+        const hipError_t e = hipLaunchKernel(eb_kernel(f64, ar64, P.lmax + 1), dim3((unsigned)(Rk.nc * split)),
+                                             dim3(cfg.threads), args, cfg.lds, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t eb_set_lds_limit(int lim) {

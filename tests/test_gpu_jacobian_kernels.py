@@ -301,3 +301,27 @@ def test_noalloc_call_after_a_change_of_arithmetic():
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(out, ref))
     sp.close()
+
+
+def test_more_centers_than_one_launch_holds():
+    """8.4 million centers at 512 threads each are more threads than a launch may
+    have.  All but three of them are one isolated atom."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    nc = 2 ** 32 // 512 + 3
+    pos = torch.tensor([[0.0, 0, 0], [50, 0, 0], [51.1, 0.4, -0.3], [50.2, -0.9, 0.8]], device="cuda")
+    Z = torch.tensor([8, 8, 1, 1], dtype=torch.int32, device="cuda")
+    print("[kernels] many centers", flush=True)
+    blocks = []
+    for centers in (torch.arange(4, dtype=torch.int32), torch.zeros(nc, dtype=torch.int32)):
+        centers[-3:] = torch.arange(1, 4, dtype=torch.int32)
+        sp = Soap((1, 8), 4.0, 9, 0, 0.5, "polynomial")
+        assert sp.build_neighbors(pos, Z, centers.cuda()) == 6
+        desc, edge, own = sp.derivatives()
+        assert sp.get_option("jacobian_kernel") == 1
+        blocks.append([edge.clone(), desc[-4:].clone(), own[-4:].clone()])
+        sp.close()
+        del desc, edge, own
+    torch.cuda.empty_cache()
+    for a, b in zip(*blocks):
+        assert a.abs().max() > 0 and torch.equal(a, b)
