@@ -133,7 +133,9 @@ struct soap_ctx {
     bool dens_ok[3] = {false, false, false}, out_ok = false, jac_ok = false;
     JacLaunch jac_cfg{};
     bool inline_radial = false; // the Jacobian path evaluates the radial factors in its kernels (no radial pass)
-    EdgeBlocksLaunch eb_cfg{}; // the edge Jacobian kernel (threads 0: k_jacobian)
+    EdgeBlocksLaunch eb_cfg{}; // k_edge_blocks (threads 0: no plan), which use_eb chooses or leaves to k_jacobian
+    bool wave_tiles = false;   // k_jacobian in its place where the centers are many (use_eb)
+    int ncu = 256;
     DescLaunch desc_cfg{};
     DjacLaunch djac_cfg{};
     int djac_tile = 0; // option "djac_tile": 0 auto (default), -1 never k_djac, else the widest chunk
@@ -445,6 +447,9 @@ int plan_launches(soap_ctx *c) {
     // an explicit "jac_tile" asks for the kernel with that tile
     c->eb_cfg = EdgeBlocksLaunch{};
     if (c->jac_tile == 0 && !c->inline_radial) (void)eb_plan(Pb, f64, ar64, &c->eb_cfg);
+    c->ncu = ncu;
+    c->wave_tiles = !f64 && bestW == jacobian_max_w() && P.S * P.n < 16 &&
+                    jacobian_blocks_per_cu(f64, ar64, Pb.rbf, P.n, P.lmax + 1, c->jac_cfg.lds) >= 4;
     // the radial pass's table, at the staging precision
     P.rtab = nullptr;
     P.rtab_k = radial_table_intervals(P, st64);
@@ -814,6 +819,20 @@ bool use_mx(const soap_ctx *c) {
     return c->mx_cfg.W > 0 && (double)c->E >= MX_MIN_RUN * (double)c->nc * (double)c->P.S;
 }
 
+// The edge Jacobian kernel of the buffered factors: k_edge_blocks, whose
+// workgroup shares a center's chunk, or k_jacobian, each wave with tiles of its
+// own.  k_jacobian is the faster one where every CU has two centers or more and
+// the basis leaves room for four workgroups of its widest tiles, with float32
+// outputs and one column tile not full (whole step, S = 2, factors from the
+// radial pass, against k_edge_blocks: 250 and more waters, n_max 2..6 with l_max
+// down from 5 to 2, 0.84 to 0.95 of its time; 160 waters 0.96 to 1.02; 66 waters
+// 1.05 to 1.15; n_max 8 0.98 to 1.03; three workgroups, n_max 4, l_max 5, 0.99
+// in float32 and 1.05 in float64 arithmetic; float64 outputs 0.95 to 1.03).  By the
+// whole list's centers: a center's results do not depend on its batch.
+bool use_eb(const soap_ctx *c) {
+    return c->eb_cfg.threads > 0 && !(c->wave_tiles && c->nc >= 2 * (int64_t)c->ncu);
+}
+
 Params params_for(const soap_ctx *c, int mode) {
     Params P = c->P;
     if (reads_radial(c, mode)) P.rbf = RBF_BUFFERED;
@@ -987,12 +1006,12 @@ int soap_get_option(const soap_ctx *c, const char *key, int64_t *value) {
                                                   : c->djac_cfg.W > 0 ? c->djac_cfg.lds
                                                                     : (c->djs_cfg.W > 0 ? c->djs_cfg.lds
                                                                                         : c->dens_cfg[1].lds))},
-               {"jacobian_tile", c->eb_cfg.threads > 0 ? 4 * c->eb_cfg.Q : c->jac_cfg.W},
-               {"jacobian_lds", (int64_t)(c->eb_cfg.threads > 0 ? c->eb_cfg.lds : c->jac_cfg.lds)},
+               {"jacobian_tile", use_eb(c) ? 4 * c->eb_cfg.Q : c->jac_cfg.W},
+               {"jacobian_lds", (int64_t)(use_eb(c) ? c->eb_cfg.lds : c->jac_cfg.lds)},
                {"output_lds", (int64_t)c->out_plan.lds},
                {"descriptor_kernel", c->desc_cfg.W > 0 ? 1 : 0},
                // 0 k_density, 1 k_djac, 2 k_djs (then the output kernel)
-               {"jacobian_kernel", c->eb_cfg.threads > 0}, // 0 k_jacobian, 1 k_edge_blocks
+               {"jacobian_kernel", use_eb(c)}, // 0 k_jacobian, 1 k_edge_blocks
                {"jacobian_density_kernel", use_mx(c) ? 3 : (c->djac_cfg.W > 0 ? 1 : (c->djs_cfg.W > 0 ? 2 : 0))}};
     for (const auto &t : tab)
         if (!std::strcmp(key, t.k)) {
@@ -1497,7 +1516,7 @@ static hipError_t run_jacobian(const soap_ctx *c, int64_t first, int64_t cf, int
                                void *jac_edge, hipStream_t st) {
     const Params P = params_for(c, 1);
     const Rows R = rows_part(c, first, cf, cn);
-    if (c->eb_cfg.threads > 0)
+    if (use_eb(c))
         return launch_edge_blocks(P, R, c->pos, c->built_f64, c->ar64, c->eb_cfg, (double)c->E / (double)c->nc, scratch,
                                   jac_edge, st);
     return launch_jacobian(P, R, c->pos, c->built_f64, c->ar64, c->jac_cfg, scratch, jac_edge, st);

@@ -325,3 +325,27 @@ def test_more_centers_than_one_launch_holds():
     torch.cuda.empty_cache()
     for a, b in zip(*blocks):
         assert a.abs().max() > 0 and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("rbf,n,l,arith", [("gto", 3, 2, "fp64"), ("gto", 5, 3, "fp64"), ("polynomial", 2, 4, "mixed"),
+                                           ("polynomial", 7, 3, "mixed"), ("polynomial", 4, 2, "fp64"),
+                                           ("polynomial-laplace", 3, 5, "mixed")])
+def test_wave_tiles_of_small_bases(rbf, n, l, arith):
+    """Small bases on 512 centers and more take the edge Jacobian kernel of wave
+    tiles, on fewer the one of whole workgroups; a batch of the list takes its
+    kernel, with the same bits."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    wl = _wl((1, 8), rbf, n, l, r_cut=3.5)
+    for atoms, kernel in ((511, 1), (512, 0)):
+        st = workloads.random_small(atoms, 6, 8.5, species=(1, 8), dmin=0.8)
+        sp = Soap(wl.species, wl.r_cut, n, l, wl.sigma, rbf, arith=arith)
+        sp.build_neighbors(torch.from_numpy(st.pos).cuda(), torch.from_numpy(st.Z).cuda())
+        assert sp.get_option("jacobian_kernel") == kernel
+        row = sp.neighbors()[0].cpu().numpy()
+        desc, edge, own = sp.derivatives()
+        b = sp.derivatives_batch(100, 57, int(row[157] - row[100]))
+        assert torch.equal(b[0], desc[100:157]) and torch.equal(b[1], edge[row[100]:row[157]])
+        assert torch.equal(b[2], own[100:157])
+        sp.close()
+        _check(wl, workloads.Structure(st.pos, st.Z, 0.0, 0), "float32", arith, centers=None if atoms == 512 else [0, 3])
