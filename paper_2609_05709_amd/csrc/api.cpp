@@ -110,7 +110,6 @@ struct soap_ctx {
     PeriodicCell cell{};
     int64_t n_ext = 0;
     DevBuf b_img_lohi, b_img_cnt, b_img_start, b_pos_ext, b_Z_ext, b_map_atom, b_map_img, b_iota;
-    WorkBase work_epoch{}; // per l-group: density work-counter increments since the counters were zeroed
     int32_t *h_flags = nullptr; // pinned: [0..3] flags, int64 E at byte 16, int64 image count at byte 32
     // pinned coherent record that the neighbour search's degree scan writes
     // (error bits | largest degree << 32, rows above TCAP, E, sequence number)
@@ -1092,7 +1091,6 @@ static int build_rows(soap_ctx *c, int64_t n_atoms, int64_t center_bound, const 
     e = nbr_phase1(w, n_atoms, center_bound, pos_dev, f64, Z_dev, c->d_lut.as<int8_t>(), c->b_spec.as<uint8_t>(),
                    n_centers, centers_dev, c->r_cut, row, st, c->d_rec, seq, &rec_written);
     if (e != hipSuccess) return hip_fail(c, e, "neighbour search");
-    c->work_epoch = WorkBase{}; // the density work counters were zeroed with the flags
     // With a rows buffer from an earlier build, the short rows are packed
     // before the host reads the total: the GPU works through the round trip.
     // k_pack writes nothing if the total exceeds the buffer; it runs again
@@ -1446,7 +1444,7 @@ static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void
         cfg.blocks = std::max(1, std::min(cfg.blocks, ncu * wg_per_cu / std::max(1, P.n_groups)));
     }
     hipError_t e = launch_density(P, rows_part(c, origin, first, count), c->pos, c->built_f64, c->ar64, mode, cfg,
-                                  c->nw.work, &c->work_epoch, desc, c_out, jself, scratch, jc_edge, to_stream(stream));
+                                  c->nw.work, desc, c_out, jself, scratch, jc_edge, to_stream(stream));
     if (e != hipSuccess) return hip_fail(c, e, "density kernel");
     if (mode == 1 && P.n_groups > 1) { // with one l-group the density kernel writes desc and jself
         e = launch_outputs(P, c->out_plan, count, c->built_f64, scratch, desc, jself, to_stream(stream));

@@ -914,9 +914,8 @@ __device__ __forceinline__ void power_tiles4(const double *__restrict__ X, int x
 //
 // Persistent: a workgroup is bound to one l-group g (blockIdx % G), keeps
 // that group's basis tables in LDS, and takes centers from an atomic work
-// counter after a first, static one (64-bit, zeroed with the neighbour list
-// and never reset between launches: a launch subtracts the count taken
-// before it, base).  Per center, each wave runs its own tiles of W edges: staging
+// counter after a first, static one (64-bit, zeroed with the neighbour list;
+// every launch leaves it at zero again).  Per center, each wave runs its own tiles of W edges: staging
 // (harmonics, gradients, radial factors) in the wave's LDS, then every lane
 // adds each edge's contribution to the coefficient entries (a, lm) it owns,
 // in registers that persist over the wave's tiles:
@@ -978,7 +977,7 @@ constexpr int dens_min_waves(int mode, bool hi) { return hi && mode == 2 ? 2 : 1
 // for float64 arithmetic with float32 outputs), and of the coefficient scratch.
 template <typename PosT, typename OutT, int MODE, int RBF, bool HI, typename ST = OutT>
 __global__ __launch_bounds__(BSD, dens_min_waves(MODE, HI)) void k_density(Params P, Rows R, const PosT *__restrict__ pos, int W,
-                                                 unsigned long long *__restrict__ work, WorkBase base,
+                                                 unsigned long long *__restrict__ work,
                                                  OutT *__restrict__ desc,
                                                  OutT *__restrict__ c_out, OutT *__restrict__ jself,
                                                  ST *__restrict__ c_scratch, OutT *__restrict__ jc_edge) {
@@ -1064,7 +1063,14 @@ __global__ __launch_bounds__(BSD, dens_min_waves(MODE, HI)) void k_density(Param
             ci = blockIdx.x / G;
             first = false;
         } else {
-            if (tid == 0) s_next = per_group + (int64_t)(atomicAdd(&work[g], 1ull) - base.b[g]);
+            if (tid == 0) {
+                // a launch takes n_c numbers of each group: every center's but the
+                // static ones, and an empty one per workgroup.  The last one clears
+                // the counter, so that a launch finds it at zero, a replayed one too.
+                const int64_t k = (int64_t)atomicAdd(&work[g], 1ull);
+                if (k == R.nc - 1) atomicExch(&work[g], 0ull);
+                s_next = per_group + k;
+            }
             lds_barrier();
             ci = __builtin_amdgcn_readfirstlane((int)s_next); // uniform: scalar addressing
             lds_barrier();                                    // s_next is rewritten by the next fetch

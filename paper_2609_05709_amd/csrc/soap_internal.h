@@ -69,16 +69,6 @@ struct Rows {
     const int64_t *e_origin;  // row offset of the output batch's first center
 };
 
-// Density work counters: one 64-bit counter per l-group, zeroed at the
-// neighbour build and never reset in between.  Every density launch advances
-// the counters of the groups it runs by exactly n_c (its centers but the
-// static first ones, plus one empty fetch per workgroup), so each group keeps
-// its own count of the increments taken so far; a launch planning fewer
-// groups leaves the other counters, and their counts, untouched.
-struct WorkBase {
-    uint64_t b[MAX_GROUPS];
-};
-
 // ---- neighbour search (neighbors.hip) ----
 constexpr int TCAP = 128; // neighbours per center kept by the collecting pass (longer rows: second pass)
 
@@ -206,14 +196,13 @@ hipError_t set_lds_limits();
 
 // desc (may be NULL; descriptor path), c_out (may be NULL, dtype), c_scratch (jac only, float64,
 // [center][c, Dx, Dy, Dz][lm][species n])
-// work: per-group counters (WorkBase); *epoch holds each group's count of
-// the increments made since they were zeroed (advanced here for the groups
-// the launch runs).
+// work: one 64-bit counter per l-group, zeroed at the neighbour build; every
+// launch leaves those of its groups at zero.
 // mode 0: descriptor (desc, c_out may be NULL); 1: descriptor + Jacobian (desc,
 // jself, c_scratch); 2: coefficient Jacobian (c_out, jself = [n_c][3][S][n][L],
 // jc_edge = [E][3][n][L])
 hipError_t launch_density(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64, int mode,
-                          const DensityLaunch &cfg, unsigned long long *work, WorkBase *epoch, void *desc, void *c_out,
+                          const DensityLaunch &cfg, unsigned long long *work, void *desc, void *c_out,
                           void *jself, void *c_scratch, void *jc_edge, hipStream_t st);
 // power spectrum and center block from the coefficient scratch (Jacobian
 // path): whole rows (rows = true: c and one component of D for every l in

@@ -240,24 +240,16 @@ hipError_t set_lds_limits() {
 }
 
 hipError_t launch_density(const Params &P, const Rows &R, const void *pos, bool f64, bool ar64, int mode,
-                          const DensityLaunch &cfg, unsigned long long *work, WorkBase *epoch, void *desc, void *c_out,
+                          const DensityLaunch &cfg, unsigned long long *work, void *desc, void *c_out,
                           void *jself, void *c_scratch, void *jc_edge, hipStream_t st) {
     if (R.nc <= 0) return hipSuccess;
     const int64_t per_group = std::min<int64_t>(R.nc, (int64_t)cfg.blocks);
-    WorkBase b = *epoch;
     Params Pk = P;
     Rows Rk = R;
     int W = cfg.W;
-    void *args[] = {&Pk, &Rk, &pos, &W, &work, &b, &desc, &c_out, &jself, &c_scratch, &jc_edge};
+    void *args[] = {&Pk, &Rk, &pos, &W, &work, &desc, &c_out, &jself, &c_scratch, &jc_edge};
     const void *k = density_kernel(f64, ar64, mode, P.rbf, cfg.hi);
-    const hipError_t e =
-        hipLaunchKernel(k, dim3((unsigned)(per_group * P.n_groups)), dim3(BSD), args, cfg.lds, st);
-    // each group's counter is taken for every center but the per_group
-    // static ones, plus one final, empty fetch per workgroup: n_c increments
-    // for every group this launch runs, none for the others
-    if (e == hipSuccess)
-        for (int g = 0; g < P.n_groups; ++g) epoch->b[g] += (uint64_t)R.nc;
-    return e;
+    return hipLaunchKernel(k, dim3((unsigned)(per_group * P.n_groups)), dim3(BSD), args, cfg.lds, st);
 }
 
 bool desc_shape(const Params &P, int *qt, int *na, int *sr) {

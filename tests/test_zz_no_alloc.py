@@ -66,6 +66,40 @@ def test_noalloc_matches_batch_entry_point():
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("rbf,n,l,tile", [("gto", 4, 3, 0), ("gto", 4, 3, -1),  # the shared density kernel
+                                          ("polynomial-laplace", 4, 2, 0)])
+def test_captured_call_replays(rbf, n, l, tile):
+    """The call captured into a graph gives the eager call's outputs at every
+    replay, with eager calls of the same context between them."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    st = workloads.random_small(700, 4, 9.0, species=(1, 8), dmin=0.9)
+    sp = Soap((1, 8), 3.5, n, l, 0.5, rbf)
+    sp.set_option("djac_tile", tile)
+    sp.set_option("djs_tile", tile)
+    # more centers than the persistent workgroups that stay resident
+    centers = torch.arange(3500, dtype=torch.int32, device="cuda") % 700
+    sp.build_neighbors(torch.from_numpy(st.pos).cuda(), torch.from_numpy(st.Z).cuda(), centers)
+    if tile < 0:
+        assert sp.get_option("jacobian_density_kernel") == 0
+    ref = [t.clone() for t in sp.derivatives()]
+    out = [torch.empty_like(t) for t in ref]
+    torch.cuda.synchronize()
+    print(f"[noalloc] capture {rbf} n{n} l{l} {tile}", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert sp._L.soap_derivatives_batch_noalloc(sp._h, 0, 3500, *(t.data_ptr() for t in out), stream) == 0
+    for _ in range(4):
+        for t in out:
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, ref))
+        assert all(torch.equal(a, b) for a, b in zip(sp.derivatives(), ref))
+    sp.close()
+
+
 def test_noalloc_refuses_batches_above_the_static_scratch():
     import torch
     from paper_2609_05709_amd.soap import RBF_CODES, SOAP_ECAPACITY, SOAP_OK, load_library
