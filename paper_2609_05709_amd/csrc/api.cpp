@@ -133,6 +133,8 @@ struct soap_ctx {
     JacLaunch jac_cfg{};
     bool inline_radial = false; // the Jacobian path evaluates the radial factors in its kernels (no radial pass)
     EdgeBlocksLaunch eb_cfg{}; // k_edge_blocks (threads 0: no plan), which use_eb chooses or leaves to k_jacobian
+    DensityLaunch lap_dens{};  // Laplace form of small l_max on many centers (own_laplace; W 0: no plan)
+    JacLaunch lap_jac{};
     bool wave_tiles = false;   // k_jacobian in its place where the centers are many (use_eb)
     int ncu = 256;
     DescLaunch desc_cfg{};
@@ -362,6 +364,20 @@ int plan_launches(soap_ctx *c) {
         const int b = plan_jacobian(P);
         c->inline_radial = c->jac_tile > 0 ? b > 0 // asks for k_jacobian
                                            : !ar64 && b >= (f64 ? 4 : 6);
+    }
+    // The Laplace form evaluated in k_density and k_jacobian, for own_laplace: one
+    // l-group, at three workgroups of two-edge tiles or more per CU
+    c->lap_dens = DensityLaunch{};
+    const int lap_l = st64 ? (P.n <= 4 || (f64 && P.n >= 8) ? 4 : 3) : (P.n <= 2 ? 6 : 4); // (own_laplace)
+    if (P.rbf == 2 && c->lmax <= lap_l && c->djac_tile == 0 && c->djs_tile == 0 && c->jac_tile == 0) {
+        const int by_regs = std::max(1, density_blocks_per_cu(f64, ar64, 1, 2, true, 0));
+        const size_t budget = std::min(LDS_HARD_LIMIT, (size_t)(159 * 1024) / (size_t)by_regs);
+        int lg[MAX_GROUPS + 1], G = 0, W = 0;
+        size_t ld = 0;
+        if (plan_groups(P, 1, st64, budget, lg, &G, &W, &ld) == 0 && G == 1 && W >= 2 && plan_jacobian(P) > 0) {
+            c->lap_dens = DensityLaunch{W, ld, ncu * density_blocks_per_cu(f64, ar64, 1, 2, true, ld), true};
+            c->lap_jac = c->jac_cfg;
+        }
     }
     if (!c->inline_radial) plan_jacobian(Pb);
     // descriptor kernel: the widest chunk of edges that keeps at least two
@@ -768,11 +784,28 @@ size_t scratch_bytes_per_center(const soap_ctx *c) {
     return elt * 4 * (size_t)c->P.S * c->P.n * c->P.L;
 }
 
+// The Jacobian path of the Laplace form with its factors evaluated in k_density
+// and k_jacobian: faster than the radial pass and the kernels after it where
+// the basis is small and the centers are many.  Time of the latter over that of
+// the former (S = 2), 500 and 1000 waters: float32 l_max 2 1.16 to 1.30 and l_max 4
+// 1.01 to 1.22 (k_jacobian is compiled for these with even n_max), l_max 0, 1, 3
+// 1.00 to 1.20, n_max 2, l_max 6 1.15, l_max 5 and the other bases of 6 0.96 to 1.03; float64
+// arithmetic or outputs l_max up to 3 1.00 to 1.20, l_max 4 1.00 to 1.10 for n_max up to
+// 4, below 1 beyond, but 1.03 to 1.15 at n_max 8, 10 and 12 with float64 outputs and 1000
+// waters.  250 waters a little less, 66 waters 0.6 to 0.97 throughout;
+// 160 waters (480 centers) 0.76 to 1.05 but for n_max up to 4 in float32: 0.97 to
+// 1.14.  By the whole list's centers: a center's results do not depend on its batch.
+bool own_laplace(const soap_ctx *c) {
+    const bool st64 = c->dtype == SOAP_FP64 || c->ar64;
+    const int least = !st64 && c->n <= 4 ? 3 : (st64 && c->lmax == 4 && c->n >= 8 ? 16 : 4); // per two CUs
+    return c->lap_dens.W > 0 && 2 * c->nc >= (int64_t)least * c->ncu;
+}
+
 // whether a density mode (and the edge Jacobian kernel after mode 1) reads the
-// radial pass's factors: the Jacobian path but for inline_radial's bases, and
-// the quadrature in every mode
+// radial pass's factors: the Jacobian path but for the bases of inline_radial and
+// own_laplace, and the quadrature in every mode
 bool reads_radial(const soap_ctx *c, int mode) {
-    return (mode == 1 && !c->inline_radial) || c->P.rbf == RBF_BUFFERED;
+    return (mode == 1 && !c->inline_radial && !own_laplace(c)) || c->P.rbf == RBF_BUFFERED;
 }
 size_t radial_bytes_per_edge(const soap_ctx *c) {
     return radial_bytes_per_edge(c->P, c->dtype == SOAP_FP64 || c->ar64);
@@ -818,6 +851,13 @@ bool use_mx(const soap_ctx *c) {
     return c->mx_cfg.W > 0 && (double)c->E >= MX_MIN_RUN * (double)c->nc * (double)c->P.S;
 }
 
+// the density step of the Jacobian path: 0 k_density, 1 k_djac, 2 k_djs, 3 k_density_mx
+int density_step(const soap_ctx *c) {
+    if (own_laplace(c)) return 0;
+    if (use_mx(c)) return 3;
+    return c->djac_cfg.W > 0 ? 1 : (c->djs_cfg.W > 0 ? 2 : 0);
+}
+
 // The edge Jacobian kernel of the buffered factors: k_edge_blocks, whose
 // workgroup shares a center's chunk, or k_jacobian, each wave with tiles of its
 // own.  k_jacobian is the faster one where every CU has two centers or more and
@@ -829,7 +869,7 @@ bool use_mx(const soap_ctx *c) {
 // in float32 and 1.05 in float64 arithmetic; float64 outputs 0.95 to 1.03).  By the
 // whole list's centers: a center's results do not depend on its batch.
 bool use_eb(const soap_ctx *c) {
-    return c->eb_cfg.threads > 0 && !(c->wave_tiles && c->nc >= 2 * (int64_t)c->ncu);
+    return c->eb_cfg.threads > 0 && !own_laplace(c) && !(c->wave_tiles && c->nc >= 2 * (int64_t)c->ncu);
 }
 
 Params params_for(const soap_ctx *c, int mode) {
@@ -838,6 +878,11 @@ Params params_for(const soap_ctx *c, int mode) {
     const int G = c->groups[mode];
     P.n_groups = G;
     for (int k = 0; k <= G; ++k) P.lgrp[k] = c->lgrp[mode][k];
+    if (mode == 1 && own_laplace(c)) {
+        P.n_groups = 1;
+        P.lgrp[0] = 0;
+        P.lgrp[1] = c->lmax + 1;
+    }
     return P;
 }
 
@@ -980,6 +1025,12 @@ int soap_set_option(soap_ctx *c, const char *key, int64_t value) {
 
 int soap_get_option(const soap_ctx *c, const char *key, int64_t *value) {
     if (!c || !key || !value) return SOAP_EINVAL;
+    const int dk = density_step(c);
+    const DensityLaunch &dc = own_laplace(c) ? c->lap_dens : c->dens_cfg[1];
+    const JacLaunch &jc = own_laplace(c) ? c->lap_jac : c->jac_cfg;
+    const int64_t dens_tile = dk == 3 ? c->mx_cfg.W : (dk == 2 ? c->djs_cfg.W : (dk == 1 ? c->djac_cfg.W : dc.W));
+    const int64_t dens_lds =
+        (int64_t)(dk == 3 ? c->mx_cfg.lds : (dk == 2 ? c->djs_cfg.lds : (dk == 1 ? c->djac_cfg.lds : dc.lds)));
     const struct {
         const char *k;
         int64_t v;
@@ -998,20 +1049,15 @@ int soap_get_option(const soap_ctx *c, const char *key, int64_t *value) {
                {"out_rows", c->out_rows ? 1 : 0},
                {"output_kernel_rows", c->out_plan.rows ? 1 : 0},
                {"jacobian_l_groups", c->groups[1]},
-               {"jacobian_density_tile",
-                use_mx(c) ? c->mx_cfg.W
-                          : (c->djac_cfg.W > 0 ? c->djac_cfg.W : (c->djs_cfg.W > 0 ? c->djs_cfg.W : c->dens_cfg[1].W))},
-               {"jacobian_density_lds", (int64_t)(use_mx(c)           ? c->mx_cfg.lds
-                                                  : c->djac_cfg.W > 0 ? c->djac_cfg.lds
-                                                                    : (c->djs_cfg.W > 0 ? c->djs_cfg.lds
-                                                                                        : c->dens_cfg[1].lds))},
-               {"jacobian_tile", use_eb(c) ? 4 * c->eb_cfg.Q : c->jac_cfg.W},
-               {"jacobian_lds", (int64_t)(use_eb(c) ? c->eb_cfg.lds : c->jac_cfg.lds)},
+               {"jacobian_density_tile", dens_tile},
+               {"jacobian_density_lds", dens_lds},
+               {"jacobian_tile", use_eb(c) ? 4 * c->eb_cfg.Q : jc.W},
+               {"jacobian_lds", (int64_t)(use_eb(c) ? c->eb_cfg.lds : jc.lds)},
                {"output_lds", (int64_t)c->out_plan.lds},
                {"descriptor_kernel", c->desc_cfg.W > 0 ? 1 : 0},
                // 0 k_density, 1 k_djac, 2 k_djs (then the output kernel)
                {"jacobian_kernel", use_eb(c)}, // 0 k_jacobian, 1 k_edge_blocks
-               {"jacobian_density_kernel", use_mx(c) ? 3 : (c->djac_cfg.W > 0 ? 1 : (c->djs_cfg.W > 0 ? 2 : 0))}};
+               {"jacobian_density_kernel", dk}};
     for (const auto &t : tab)
         if (!std::strcmp(key, t.k)) {
             *value = t.v;
@@ -1327,8 +1373,10 @@ int soap_get_neighbors(soap_ctx *c, int64_t *row_ptr_dev, int32_t *cols_dev, voi
 // edge Jacobian kernel, and the output kernel when the density kernel splits
 // l into groups; the one-workgroup-per-center kernel needs neither split)
 static bool jacobian_path_ok(const soap_ctx *c, int mode) {
-    if (mode == 1 && c->djac_cfg.W > 0) return c->jac_ok;
-    if (mode == 1 && (c->djs_cfg.W > 0 || use_mx(c))) return c->jac_ok && c->out_ok;
+    const int step = mode == 1 ? density_step(c) : 0;
+    if (step == 1) return c->jac_ok;
+    if (step > 1) return c->jac_ok && c->out_ok;
+    if (mode == 1 && own_laplace(c)) return true;
     return c->dens_ok[mode] && (mode != 1 || (c->jac_ok && (c->groups[1] == 1 || c->out_ok)));
 }
 
@@ -1394,7 +1442,8 @@ static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void
         timer.done();
         return SOAP_OK;
     }
-    if (mode == 1 && c->djac_cfg.W > 0 && !use_mx(c)) { // one workgroup per center
+    const int step = mode == 1 ? density_step(c) : 0;
+    if (step == 1) { // one workgroup per center
         DjacLaunch dj = c->djac_cfg;
         if (wg_per_cu > 0) {
             int ncu = 256;
@@ -1407,7 +1456,7 @@ static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void
         timer.done();
         return SOAP_OK;
     }
-    if (mode == 1 && use_mx(c)) { // one workgroup per center, then the output kernel
+    if (step == 3) { // one workgroup per center, then the output kernel
         DensityMxLaunch mx = c->mx_cfg;
         if (wg_per_cu > 0) {
             int ncu = 256;
@@ -1422,7 +1471,7 @@ static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void
         timer.done();
         return SOAP_OK;
     }
-    if (mode == 1 && c->djs_cfg.W > 0) { // one workgroup per center, then the output kernel
+    if (step == 2) { // one workgroup per center, then the output kernel
         DjsLaunch dj = c->djs_cfg;
         if (wg_per_cu > 0) {
             int ncu = 256;
@@ -1437,7 +1486,7 @@ static int run_density(soap_ctx *c, int mode, int64_t first, int64_t count, void
         timer.done();
         return SOAP_OK;
     }
-    DensityLaunch cfg = c->dens_cfg[mode];
+    DensityLaunch cfg = mode == 1 && own_laplace(c) ? c->lap_dens : c->dens_cfg[mode];
     if (wg_per_cu > 0) {
         int ncu = 256;
         (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
@@ -1517,7 +1566,8 @@ static hipError_t run_jacobian(const soap_ctx *c, int64_t first, int64_t cf, int
     if (use_eb(c))
         return launch_edge_blocks(P, R, c->pos, c->built_f64, c->ar64, c->eb_cfg, (double)c->E / (double)c->nc, scratch,
                                   jac_edge, st);
-    return launch_jacobian(P, R, c->pos, c->built_f64, c->ar64, c->jac_cfg, scratch, jac_edge, st);
+    return launch_jacobian(P, R, c->pos, c->built_f64, c->ar64, own_laplace(c) ? c->lap_jac : c->jac_cfg, scratch,
+                           jac_edge, st);
 }
 
 // Pipelined descriptor + Jacobian: the batch in K center chunks; the density

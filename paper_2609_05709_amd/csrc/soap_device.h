@@ -445,7 +445,7 @@ __device__ __forceinline__ void lds_barrier() {
 //   YY: harmonics, element (edge e, component c, lm) at
 //       e es + c cs + (lm - lmY0) ls; component 0 = S, 1..3 = dS/dx_d (GRAD).
 //       Degrees from lgY0 = lg0 - 1 (GRAD and lg0 > 0) or lg0 are stored.
-//   BB[e][n][lc] = K (B_nl, Bh_nl), K = K_l if SCALE (GTO) else 1, stored at precision BT
+//   BB[e][n][lc] = K (B_nl, Bh_nl), K = K_l if SCALE (GTO, Laplace form) else 1, stored at precision BT
 //   X: GTO exponentials [e][k][lc], the polynomial table [e][q][0..lg1], or
 //      the Laplace form's P_j [e][n][j]
 // Phase 1 runs the harmonic columns (edge, m), then the radial scratch;
@@ -631,7 +631,8 @@ __device__ __forceinline__ void stage_edges(const Params &P, const Tables &T, YT
                 b = rl * f;
                 bh = rl * ir * (fp - (double)l * f * ir);
             }
-            BB[it] = Pair<BT>::make(b, bh);
+            const double K = SCALE ? T.Kl[l] : 1.0;
+            BB[it] = Pair<BT>::make(K * b, K * bh);
         }
     } else {
         // the factors the radial pass left for this call's edges (r0: the first, from *P.rad_origin)
@@ -963,15 +964,16 @@ __host__ __device__ __forceinline__ size_t dens_wave_doubles(const Params &P, in
 // 2 coefficient Jacobian ("cc": c, every edge's dc/dr_j, and -D).
 // RBF: where the radial factors come from, fixed at compile time (1 the radial
 // pass: every basis in mode 1, the polynomial quadrature in the other modes;
-// 0 GTO, 2 polynomial in the Laplace form, 3 GTO compensated: evaluated in
-// the staging of modes 0 and 2).  The other branches of the staging then drop
-// out, and with them up to 40 VGPRs: the GTO descriptor kernel runs four
-// waves per SIMD instead of three.
+// evaluated in the staging: 0 GTO and 3 GTO compensated in modes 0 and 2, 2
+// polynomial in the Laplace form in all modes).  The other branches of the
+// staging then drop out, and with them up to 40 VGPRs: the GTO descriptor
+// kernel runs four waves per SIMD instead of three.
 // Resident waves per SIMD: a second variant (HI) of the coefficient Jacobian
-// asks for 2 (it otherwise takes all 256 VGPRs and runs one wave).  More
-// workgroups per CU split the LDS further, so the host takes HI only where
-// the LDS plan allows it (plan_launches).
-constexpr int dens_min_waves(int mode, bool hi) { return hi && mode == 2 ? 2 : 1; }
+// asks for 2 (it otherwise takes all 256 VGPRs and runs one wave); the Laplace
+// form in mode 1 is compiled for 3 (a small spill).  More workgroups per CU split the
+// LDS further, so the host takes HI only where the LDS plan allows it
+// (plan_launches).
+constexpr int dens_min_waves(int mode, bool hi) { return hi ? (mode == 2 ? 2 : 3) : 1; }
 
 // ST: precision of the staged harmonics and radial factors (OutT, or double
 // for float64 arithmetic with float32 outputs), and of the coefficient scratch.
@@ -2499,15 +2501,16 @@ constexpr int jac_min_waves(int ab, int NT, int LWT) {
 // hold the radial pass's factors on entry (P.rad), which are read before they are
 // written over.
 template <typename OutT, int RBF> struct EdgeBlocks {
-    using ptr = OutT *;
-};
-template <typename OutT> struct EdgeBlocks<OutT, 0> {
     using ptr = OutT *__restrict__;
+};
+template <typename OutT> struct EdgeBlocks<OutT, RBF_BUFFERED> {
+    using ptr = OutT *;
 };
 
 // AT: precision of the final assembly (OutT, or double for float64
 // arithmetic with float32 outputs).
-// RBF: 0 the GTO factors evaluated in the staging, else the radial pass's
+// RBF: 0 the GTO factors evaluated in the staging, 2 the Laplace form's, else the
+// radial pass's
 template <typename PosT, typename OutT, int NT, int LWT, int RBF, typename AT = OutT>
 __global__ __launch_bounds__(BSJ, jac_min_waves(sizeof(AT), NT, LWT)) void k_jacobian(Params P, Rows R, const PosT *__restrict__ pos,
                                                                             int W, int vec, const AT *__restrict__ c_scratch,
@@ -2536,10 +2539,10 @@ __global__ __launch_bounds__(BSJ, jac_min_waves(sizeof(AT), NT, LWT)) void k_jac
     // this wave's private staging
     Carver wv{cv.take(0) + (size_t)wave * jac_wave_doubles(P, W, ab)};
     double *YY = wv.take((size_t)W * 4 * L); // [e][S, dS/dx, dS/dy, dS/dz][L]
-    // K_l multiplies the factors where they are evaluated here (GTO), else the
+    // K_l multiplies the factors where they are evaluated here, else the
     // precontraction results (float32 GTO n_max 10, l_max 5, 66 waters: 98.5
     // against 103 us)
-    constexpr bool KB = RBF == 0;
+    constexpr bool KB = RBF != RBF_BUFFERED;
     AT2 *BB = (AT2 *)wv.take(2 * (size_t)W * nl * ab / 8); // [e][n][l] = (B, Bh)
     double *XU = wv.take((size_t)W * jac_xu_doubles(P, ab));
     // precontraction results, aliasing the radial scratch: U2a[e][u][l] =

@@ -148,7 +148,7 @@ struct DensityLaunch {
     int W;           // edges per wave iteration
     size_t lds;      // dynamic LDS bytes
     int blocks;      // persistent workgroups per l-group
-    bool hi;         // the variant compiled for two waves per SIMD (mode 2)
+    bool hi;         // the variant compiled for two waves per SIMD (mode 2) or three (mode 1, Laplace form)
 };
 struct DescLaunch {
     int W;          // edges per chunk (0: the descriptor path uses k_density)
@@ -187,11 +187,11 @@ size_t jacobian_lds_bytes(const Params &P, int W, bool at64); // at64: float64 a
 int jacobian_max_w();
 // resident workgroups per CU (0 if it does not fit)
 int jacobian_blocks_per_cu(bool f64, bool ar64, int rbf, int n, int lw, size_t lds);
-bool jacobian_has_fixed(int n, int lw); // a float32 GTO kernel compiled for this basis size
-// float32 Jacobian kernels for fixed (n_max, l_max + 1); NULL if not compiled
-const void *jacobian_fixed_0(int n, int lw);
-const void *jacobian_fixed_1(int n, int lw);
-const void *jacobian_fixed_2(int n, int lw);
+// float32 Jacobian kernels for fixed (n_max, l_max + 1), factors of rbf 0 or 2
+// evaluated in the kernel; NULL if not compiled
+const void *jacobian_fixed_0(int rbf, int n, int lw);
+const void *jacobian_fixed_1(int rbf, int n, int lw);
+const void *jacobian_fixed_2(int rbf, int n, int lw);
 hipError_t set_lds_limits();
 
 // desc (may be NULL; descriptor path), c_out (may be NULL, dtype), c_scratch (jac only, float64,

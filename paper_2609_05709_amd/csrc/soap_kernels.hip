@@ -16,12 +16,14 @@ size_t density_lds_bytes(const Params &P, int jac, int lg0, int lg1, int W, bool
 
 // the density kernel of a precision (positions and outputs T, staging ST),
 // mode, radial basis and occupancy variant
-// (mode 1 reads the radial pass's factors for every basis)
+// (mode 1 reads the radial pass's factors for every basis; the Laplace form
+// also evaluates its own)
 template <typename T, typename ST, int RBF>
 static const void *density_kernel_r(int mode, bool hi) {
     if (mode == 0) return (const void *)dev::k_density<T, T, 0, RBF, false, ST>;
     if (mode == 1) {
         if constexpr (RBF == RBF_BUFFERED) return (const void *)dev::k_density<T, T, 1, RBF, false, ST>;
+        if constexpr (RBF == 2) return (const void *)dev::k_density<T, T, 1, RBF, true, ST>;
         return nullptr;
     }
     return hi ? (const void *)dev::k_density<T, T, 2, RBF, true, ST>
@@ -167,25 +169,24 @@ hipError_t launch_outputs(const Params &P, const OutPlan &O, int64_t nc, bool f6
 
 int jacobian_max_w() { return JAC_MAX_W; }
 
-// rbf 0: the GTO factors evaluated in the kernel; RBF_BUFFERED: the radial
-// pass's.  The float32 GTO kernel is also compiled for fixed (n_max, l_max +
-// 1) pairs (jacobian_fixed.hip).
-static const void *jacobian_fixed(int n, int lw) {
-    const void *k = jacobian_fixed_0(n, lw);
-    if (!k) k = jacobian_fixed_1(n, lw);
-    return k ? k : jacobian_fixed_2(n, lw);
+// rbf 0, 2: the GTO's or Laplace form's factors evaluated in the kernel;
+// RBF_BUFFERED: the radial pass's.  The float32 kernels of the former are also
+// compiled for fixed (n_max, l_max + 1) pairs (jacobian_fixed.hip).
+static const void *jacobian_fixed(int rbf, int n, int lw) {
+    const void *k = jacobian_fixed_0(rbf, n, lw);
+    if (!k) k = jacobian_fixed_1(rbf, n, lw);
+    return k ? k : jacobian_fixed_2(rbf, n, lw);
 }
-bool jacobian_has_fixed(int n, int lw) { return jacobian_fixed(n, lw) != nullptr; }
+template <int RBF> static const void *jacobian_kernel_r(bool f64, bool ar64) {
+    if (f64) return reinterpret_cast<const void *>(&k_jacobian<double, double, 0, 0, RBF>);
+    return ar64 ? reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, RBF, double>)
+                : reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, RBF>);
+}
 const void *jacobian_kernel(bool f64, bool ar64, int rbf, int n, int lw) {
-    if (rbf != 0) {
-        if (f64) return reinterpret_cast<const void *>(&k_jacobian<double, double, 0, 0, RBF_BUFFERED>);
-        return ar64 ? reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, RBF_BUFFERED, double>)
-                    : reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, RBF_BUFFERED>);
-    }
-    if (f64) return reinterpret_cast<const void *>(&k_jacobian<double, double, 0, 0, 0>);
-    if (ar64) return reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, 0, double>);
-    const void *k = jacobian_fixed(n, lw);
-    return k ? k : reinterpret_cast<const void *>(&k_jacobian<float, float, 0, 0, 0>);
+    const void *k = (rbf == RBF_BUFFERED || f64 || ar64) ? nullptr : jacobian_fixed(rbf, n, lw);
+    if (k) return k;
+    return rbf == 0 ? jacobian_kernel_r<0>(f64, ar64)
+                    : (rbf == 2 ? jacobian_kernel_r<2>(f64, ar64) : jacobian_kernel_r<RBF_BUFFERED>(f64, ar64));
 }
 
 int jacobian_blocks_per_cu(bool f64, bool ar64, int rbf, int n, int lw, size_t lds) {
@@ -228,10 +229,11 @@ hipError_t set_lds_limits() {
     SOAP_SET(k_power_single<float>);
     SOAP_SET(k_power_single<double>);
     for (int v = 0; v < 3; ++v)
-        for (int rbf : {0, RBF_BUFFERED}) SOAP_SET(jacobian_kernel(v == 2, v == 1, rbf, NMAX, LMAX + 1));
+        for (int rbf : {0, 2, RBF_BUFFERED}) SOAP_SET(jacobian_kernel(v == 2, v == 1, rbf, NMAX, LMAX + 1));
     for (int n = 1; n <= NMAX; ++n)
         for (int lw = 1; lw <= LMAX + 1; ++lw)
-            if (jacobian_has_fixed(n, lw)) SOAP_SET(jacobian_fixed(n, lw));
+            for (int rbf : {0, 2})
+                if (jacobian_fixed(rbf, n, lw)) SOAP_SET(jacobian_fixed(rbf, n, lw));
 #undef SOAP_SET
     if (e == hipSuccess) e = djs_set_lds_limit(lim);
     if (e == hipSuccess) e = radial_set_lds_limit(lim);

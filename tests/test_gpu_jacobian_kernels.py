@@ -349,3 +349,28 @@ def test_wave_tiles_of_small_bases(rbf, n, l, arith):
         assert torch.equal(b[2], own[100:157])
         sp.close()
         _check(wl, workloads.Structure(st.pos, st.Z, 0.0, 0), "float32", arith, centers=None if atoms == 512 else [0, 3])
+
+
+@pytest.mark.parametrize("n,l,dtype,arith,least", [(2, 2, "float32", "mixed", 384), (4, 4, "float32", "mixed", 384),
+                                                   (6, 3, "float32", "mixed", 512), (2, 6, "float32", "mixed", 384),
+                                                   (3, 4, "float32", "fp64", 512), (5, 3, "float64", "mixed", 512)])
+def test_laplace_form_in_the_kernels(n, l, dtype, arith, least):
+    """The Laplace form of small bases is evaluated in the density and edge
+    Jacobian kernels from a number of centers on, by the radial pass below it;
+    a batch of the list takes its kernels, with the same bits."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    wl = _wl((1, 8), "polynomial-laplace", n, l, r_cut=3.5)
+    tdt = torch.float64 if dtype == "float64" else torch.float32
+    for atoms in (least - 1, least):
+        st = workloads.random_small(atoms, 6, 8.5, species=(1, 8), dmin=0.8)
+        sp = Soap(wl.species, wl.r_cut, n, l, wl.sigma, wl.rbf, dtype=dtype, arith=arith)
+        sp.build_neighbors(torch.from_numpy(st.pos).to("cuda", tdt), torch.from_numpy(st.Z).cuda())
+        assert (sp.get_option("jacobian_density_kernel") == 0) == (atoms == least)
+        row = sp.neighbors()[0].cpu().numpy()
+        desc, edge, own = sp.derivatives()
+        b = sp.derivatives_batch(100, 57, int(row[157] - row[100]))
+        assert torch.equal(b[0], desc[100:157]) and torch.equal(b[1], edge[row[100]:row[157]])
+        assert torch.equal(b[2], own[100:157])
+        sp.close()
+        _check(wl, workloads.Structure(st.pos, st.Z, 0.0, 0), dtype, arith)
