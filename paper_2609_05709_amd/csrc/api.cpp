@@ -427,9 +427,19 @@ int plan_launches(soap_ctx *c) {
     // the other bases: coefficients streamed to the scratch, outputs by the
     // output kernel.  The widest chunk of edges that keeps at least two
     // workgroups resident per CU.
+    //
+    // Larger bases of more species also where k_djac would fit: its block of
+    // coefficients (4 S n (l_max+1)^2) leaves it two workgroups per CU, whose four
+    // waves then form the power spectrum of (S n)^2 pairs per degree.  Density step
+    // of k_djs over that of k_djac, S = 3 and 4, 500 to 4096 centers of 5 to 50 edges, by
+    // S n (l_max+1): float64 outputs 96 to 128 0.99 to 1.5, 144 0.67 to 1.07, 160 0.69 to
+    // 1.04, 200 0.48 to 0.77; float32 192 and 216 0.91 to 1.2, 240 0.71 to 1.04 (1.11 in
+    // one), 280 0.76 to 1.0.  S n up to 24: 1.05 and more, but for the last degrees.
+    const bool streamed = !c->inline_radial && c->djac_tile == 0 && P.S * P.n >= 32 &&
+                          P.S * P.n * (P.lmax + 1) >= (f64 ? 144 : 240);
     c->djs_cfg = DjsLaunch{};
     int qs = 0;
-    if (c->djac_cfg.W == 0 && c->djs_tile >= 0 && c->out_ok && djs_shape(Pb, &qs)) {
+    if ((c->djac_cfg.W == 0 || streamed) && c->djs_tile >= 0 && c->out_ok && djs_shape(Pb, &qs)) {
         for (int W : {64, 32, 16}) {
             if (c->djs_tile > 0 && W > c->djs_tile) continue;
             const size_t lds = djs_lds_bytes(Pb, W, st64);
@@ -440,6 +450,7 @@ int plan_launches(soap_ctx *c) {
                 break;
             }
         }
+        if (c->djs_cfg.W > 0) c->djac_cfg = DjacLaunch{};
     }
     // k_density_mx, where k_djac has no plan or two tasks per thread, and no
     // option asks for another kernel; one workgroup per CU where nothing else fits

@@ -374,3 +374,24 @@ def test_laplace_form_in_the_kernels(n, l, dtype, arith, least):
         assert torch.equal(b[2], own[100:157])
         sp.close()
         _check(wl, workloads.Structure(st.pos, st.Z, 0.0, 0), dtype, arith)
+
+
+# S n (l_max + 1) below and from 240 on (float64 outputs 144), at S n >= 32
+@pytest.mark.parametrize("rbf,n,l,dtype,arith,kernel",
+                         [("polynomial", 9, 5, "float32", "mixed", 1), ("polynomial", 10, 5, "float32", "mixed", 2),
+                          ("gto", 12, 4, "float32", "fp64", 2), ("polynomial-laplace", 8, 3, "float64", "mixed", 1),
+                          ("gto", 12, 2, "float64", "mixed", 2), ("polynomial", 9, 6, "float64", "mixed", 2)])
+def test_streamed_coefficients_of_several_species(rbf, n, l, dtype, arith, kernel):
+    """Bases of many radial functions and species stream their coefficients to
+    the output kernel on short rows, with the explicit choice left alone."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    wl = _wl((1, 6, 7, 8), rbf, n, l, r_cut=3.5)
+    st = workloads.random_small(150, 6, 6.5, species=(1, 6, 7, 8), dmin=0.8)
+    sp = Soap(wl.species, wl.r_cut, n, l, wl.sigma, rbf, dtype=dtype, arith=arith)
+    sp.build_neighbors(torch.from_numpy(st.pos).to("cuda", sp.dtype), torch.from_numpy(st.Z).cuda())
+    assert sp.get_option("jacobian_density_kernel") == kernel
+    sp.set_option("djac_tile", 32)
+    assert sp.get_option("jacobian_density_kernel") == 1
+    sp.close()
+    _check(wl, st, dtype, arith)
