@@ -135,7 +135,7 @@ struct soap_ctx {
     EdgeBlocksLaunch eb_cfg{}; // k_edge_blocks (threads 0: no plan), which use_eb chooses or leaves to k_jacobian
     DensityLaunch lap_dens{};  // Laplace form of small l_max on many centers (own_laplace; W 0: no plan)
     JacLaunch lap_jac{};
-    bool wave_tiles = false;   // k_jacobian in its place where the centers are many (use_eb)
+    int wave_tiles = 0;        // k_jacobian in its place from this many centers per CU on (use_eb; 0: never)
     int ncu = 256;
     DescLaunch desc_cfg{};
     DjacLaunch djac_cfg{};
@@ -474,8 +474,12 @@ int plan_launches(soap_ctx *c) {
     c->eb_cfg = EdgeBlocksLaunch{};
     if (c->jac_tile == 0 && !c->inline_radial) (void)eb_plan(Pb, f64, ar64, &c->eb_cfg);
     c->ncu = ncu;
-    c->wave_tiles = !f64 && bestW == jacobian_max_w() && P.S * P.n < 16 &&
-                    jacobian_blocks_per_cu(f64, ar64, Pb.rbf, P.n, P.lmax + 1, c->jac_cfg.lds) >= 4;
+    c->wave_tiles = 0;
+    if (!f64 && bestW > 0) { // (use_eb)
+        const int b = jacobian_blocks_per_cu(f64, ar64, Pb.rbf, P.n, P.lmax + 1, c->jac_cfg.lds), Sn = P.S * P.n;
+        if (b >= 4 && bestW == jacobian_max_w() && Sn < (P.S > 2 ? 25 : 16)) c->wave_tiles = 2;
+        else if (P.S > 2 && ((b >= 4 && bestW >= 3) || (Sn > 32 && b >= 3))) c->wave_tiles = 4;
+    }
     // the radial pass's table, at the staging precision
     P.rtab = nullptr;
     P.rtab_k = radial_table_intervals(P, st64);
@@ -877,10 +881,17 @@ int density_step(const soap_ctx *c) {
 // radial pass, against k_edge_blocks: 250 and more waters, n_max 2..6 with l_max
 // down from 5 to 2, 0.84 to 0.95 of its time; 160 waters 0.96 to 1.02; 66 waters
 // 1.05 to 1.15; n_max 8 0.98 to 1.03; three workgroups, n_max 4, l_max 5, 0.99
-// in float32 and 1.05 in float64 arithmetic; float64 outputs 0.95 to 1.03).  By the
+// in float32 and 1.05 in float64 arithmetic; float64 outputs 0.95 to 1.03).  With
+// three species and more a section of a block is a smaller part of it, and beyond
+// 32 coefficients per (l, m) k_edge_blocks has chunks of four edges only: there
+// k_jacobian is the faster one of more bases (kernel times, S = 3 and 4, rows of 8 to
+// 50 edges: S n up to 24 in four workgroups of four-edge tiles, 512 centers 0.78 to
+// 1.02, 1500 and more 0.67 to 0.9; S n 25 to 48 there, or three-edge tiles, 512
+// centers 0.88 to 1.3, 1500 and more 0.65 to 1.06; S n above 32, three workgroups or
+// more, 0.79 to 1.0; two-edge tiles of smaller S n 0.9 to 1.3).  By the
 // whole list's centers: a center's results do not depend on its batch.
 bool use_eb(const soap_ctx *c) {
-    return c->eb_cfg.threads > 0 && !own_laplace(c) && !(c->wave_tiles && c->nc >= 2 * (int64_t)c->ncu);
+    return c->eb_cfg.threads > 0 && !own_laplace(c) && !(c->wave_tiles > 0 && c->nc >= c->wave_tiles * (int64_t)c->ncu);
 }
 
 Params params_for(const soap_ctx *c, int mode) {

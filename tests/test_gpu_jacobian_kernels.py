@@ -395,3 +395,22 @@ def test_streamed_coefficients_of_several_species(rbf, n, l, dtype, arith, kerne
     assert sp.get_option("jacobian_density_kernel") == 1
     sp.close()
     _check(wl, st, dtype, arith)
+
+
+@pytest.mark.parametrize("species,rbf,n,l,arith,least,above",
+                         [((1, 6, 7, 8), "gto", 5, 1, "fp64", 512, 0), ((1, 6, 7, 8), "gto", 4, 2, "fp64", 512, 0),
+                          ((1, 6, 8), "polynomial", 9, 1, "mixed", 1024, 0), ((1, 6, 7, 8), "polynomial", 5, 4, "mixed", 1024, 0),
+                          ((1, 6, 7, 8), "polynomial", 12, 2, "mixed", 1024, 0), ((1, 6, 8), "polynomial", 6, 5, "mixed", 1024, 1)])
+def test_wave_tiles_of_several_species(species, rbf, n, l, arith, least, above):
+    """With three species and more the edge Jacobian kernel of wave tiles takes
+    more of the bases (above: the kernel from `least` centers on)."""
+    import torch
+    from paper_2609_05709_amd.soap import Soap
+    wl = _wl(species, rbf, n, l, r_cut=3.0)
+    for atoms, kernel in ((least - 1, 1), (least, above)):
+        st = workloads.random_small(atoms, 6, 10.5, species=species, dmin=0.8)
+        sp = Soap(wl.species, wl.r_cut, n, l, wl.sigma, rbf, arith=arith)
+        sp.build_neighbors(torch.from_numpy(st.pos).cuda(), torch.from_numpy(st.Z).cuda())
+        assert sp.get_option("jacobian_kernel") == kernel
+        sp.close()
+    _check(wl, st, "float32", arith)
