@@ -582,7 +582,14 @@ hipError_t launch_radial(const Params &P, const Rows &R, const void *pos, bool f
     return launch_radial_from(P, R, pos, f64, ar64, degree, false, st);
 }
 
-constexpr int RTAB_MAX_K = 4096;
+// Most intervals of a table (doubling with 1 / sigma).  The quadrature is the slower one
+// at any size of the table (whole step at 6144 intervals, 48 to 1500 atoms, n_max 2..12:
+// 0.68 to 0.92 of its time; at 3072 0.68 to 0.91), so there the limit is on memory: 4096
+// intervals of n_max 12, l_max 12 are 51 MB in float32 records and 82 MB in float64. The GTO
+// exponentials (but for the compensated ones) cost less than records that don't stay in the L2: density step
+// with the table over that without, 480 to 4096 centers, n_max 3..12: 192 and 384
+// intervals 0.90 to 1.01, 768 0.96 to 1.02, 1536 0.95 to 1.05, 3072 1.00 to 1.14.
+constexpr int RTAB_MAX_K = 4096, RTAB_MAX_K_GTO = 512;
 double radial_table_inv_h(const Params &P, bool st64) {
     const double h = P.sigma / (st64 ? RadRecord<double>::PER_SIGMA : RadRecord<float>::PER_SIGMA);
     return std::exp2(-std::floor(std::log2(h)));
@@ -592,7 +599,7 @@ int radial_table_intervals(const Params &P, bool st64) {
     // (128 bytes a factor) cost more than the exponentials, the float32 ones less
     if (P.rbf == 2 || (P.rbf == 0 && st64)) return 0;
     const double k = std::ceil(P.rc * radial_table_inv_h(P, st64));
-    return k <= RTAB_MAX_K ? std::max(1, (int)k) : 0;
+    return k <= (P.rbf == 0 ? RTAB_MAX_K_GTO : RTAB_MAX_K) ? std::max(1, (int)k) : 0;
 }
 size_t radial_table_bytes(const Params &P, bool st64) {
     const size_t rec = st64 ? sizeof(RadRecord<double>) : sizeof(RadRecord<float>);

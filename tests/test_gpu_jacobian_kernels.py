@@ -83,17 +83,19 @@ def test_coincident_neighbours_in_dense_rows(dtype, arith, rbf, n, l, sigma):
 
 @pytest.mark.parametrize("dtype", ["float32", "float64"])
 @pytest.mark.parametrize("rbf,sigma", [("polynomial", 0.5), ("polynomial", 0.3), ("gto", 0.5),
-                                       ("gto", 0.02), ("polynomial-laplace", 0.3)])
+                                       ("gto", 0.3), ("gto", 0.12), ("gto", 0.02),
+                                       ("polynomial-laplace", 0.3)])
 def test_radial_pass_distances(rbf, sigma, dtype):
     """Dimers over every distance: coincident, nearly so, at the table's
     interval boundaries and around them, up to the last value below the
-    cutoff.  sigma 0.02 has no table (too many intervals;
-    the oracle's Bessel functions end before the quadrature's would); the Laplace form
+    cutoff.  GTO in float32 has a table at sigma 0.3 and none at 0.12, and nothing has
+    one at 0.02 (too many intervals; the oracle's Bessel functions end before the quadrature's would); the Laplace form
     never has one and starts where it is an expansion at all."""
     rc = 5.0
-    h = rc / np.ceil(rc / sigma * 20.0)
+    h = float(np.exp2(np.floor(np.log2(sigma / (20.0 if dtype == "float64" else 16.0)))))  # an interval
+    k = np.float32(h * np.floor(2.0 / h))
     last = float(np.nextafter(np.float32(rc), np.float32(0)))
-    d = [0.5, 1.0, 2.345, h * 40, np.nextafter(h * 40, 0), np.nextafter(h * 40, 9), rc - h / 2, last]
+    d = [0.5, 1.0, 2.345, k, np.nextafter(k, np.float32(0)), np.nextafter(k, np.float32(9)), rc - h / 2, last]
     if rbf != "polynomial-laplace":
         d += [0.0, 1e-3, 0.05, h, h / 3]
     pos, Z = [], []
