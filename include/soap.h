@@ -128,7 +128,10 @@ int soap_create(const int32_t *species_Z, int32_t n_species, double r_cut, int32
  *   "dtype"  : SOAP_FP32 or SOAP_FP64 (default SOAP_FP32);
  *   "arith"  : SOAP_ARITH_MIXED (default) or SOAP_ARITH_FP64, the internal
  *              arithmetic of the float32 mode (see dtype above; the float64
- *              mode is float64 throughout either way);
+ *              mode is float64 throughout either way; the mixed arithmetic
+ *              rounds the radial factors once to float32, from float64 values
+ *              or from a table's, which are off by up to 4e-12 of their
+ *              interval's largest value);
  *   "quad_n" : Gauss-Legendre order for the polynomial basis, 8..256
  *              (default 64; Sec. 3.1, the fixed Gauss-Legendre rule on
  *              [0, r_cut]); rebuilds the quadrature table;
@@ -376,7 +379,10 @@ int soap_compute_averaged(soap_ctx *ctx, int32_t mode, void *desc_dev, void *str
  * features whose pair lacks species(j)).  Any element alignment works; in
  * float64 mode a 16-byte aligned jac_edge_dev is written with 16-byte stores
  * (faster) when both section lengths n_max^2 (l_max+1) and
- * n_max (n_max+1)/2 (l_max+1) are even.  Errors: SOAP_ESTATE, SOAP_ENOMEM,
+ * n_max (n_max+1)/2 (l_max+1) are even.  The call uses the edge blocks as scratch
+ * before it writes them (an edge's radial factors lie at the start of its block),
+ * so jac_edge_dev must be readable device memory, and nothing else may access it
+ * until the call's work on the stream is done.  Errors: SOAP_ESTATE, SOAP_ENOMEM,
  * SOAP_EHIP.
  */
 int soap_derivatives(soap_ctx *ctx, void *desc_dev, void *jac_edge_dev, void *jac_self_dev, void *stream);
