@@ -428,14 +428,17 @@ int plan_launches(soap_ctx *c) {
     // output kernel.  The widest chunk of edges that keeps at least two
     // workgroups resident per CU.
     //
-    // Larger bases of more species also where k_djac would fit: its block of
-    // coefficients (4 S n (l_max+1)^2) leaves it two workgroups per CU, whose four
-    // waves then form the power spectrum of (S n)^2 pairs per degree.  Density step
-    // of k_djs over that of k_djac, S = 3 and 4, 500 to 4096 centers of 5 to 50 edges, by
-    // S n (l_max+1): float64 outputs 96 to 128 0.99 to 1.5, 144 0.67 to 1.07, 160 0.69 to
-    // 1.04, 200 0.48 to 0.77; float32 192 and 216 0.91 to 1.2, 240 0.71 to 1.04 (1.11 in
-    // one), 280 0.76 to 1.0.  S n up to 24: 1.05 and more, but for the last degrees.
-    const bool streamed = !c->inline_radial && c->djac_tile == 0 && P.S * P.n >= 32 &&
+    // In float64 arithmetic, larger bases of more species also where k_djac would
+    // fit: its block of coefficients (4 S n (l_max+1)^2) leaves it two workgroups per
+    // CU, whose four waves then form the power spectrum of (S n)^2 pairs per degree.
+    // Density step of k_djs over that of k_djac, S = 3 and 4, 500 to 4096 centers of 5
+    // to 50 edges, by S n (l_max+1): float64 outputs 96 to 128 0.99 to 1.5, 144 0.67 to
+    // 1.07, 160 0.69 to 1.04, 200 0.48 to 0.77; float32 outputs 192 and 216 0.98 to 1.2, 240
+    // 0.73 to 1.04, 280 0.79 to 1.0.  S n up to 24: 1.05 and more, but for the last
+    // degrees.  Not in the mixed arithmetic, where it would be as much faster: the
+    // scratch is float32 there, k_djac's coefficients are float64, and the
+    // descriptor's error grew from 6.7e-8 to 7.3e-8 (n_max 10, l_max 5).
+    const bool streamed = !c->inline_radial && st64 && c->djac_tile == 0 && P.S * P.n >= 32 &&
                           P.S * P.n * (P.lmax + 1) >= (f64 ? 144 : 240);
     c->djs_cfg = DjsLaunch{};
     int qs = 0;

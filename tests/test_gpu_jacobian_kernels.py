@@ -378,14 +378,16 @@ def test_laplace_form_in_the_kernels(n, l, dtype, arith, least):
         _check(wl, workloads.Structure(st.pos, st.Z, 0.0, 0), dtype, arith)
 
 
-# S n (l_max + 1) below and from 240 on (float64 outputs 144), at S n >= 32
+# S n (l_max + 1) below and from 240 on (float64 outputs 144), at S n >= 32, in float64 arithmetic
 @pytest.mark.parametrize("rbf,n,l,dtype,arith,kernel",
-                         [("polynomial", 9, 5, "float32", "mixed", 1), ("polynomial", 10, 5, "float32", "mixed", 2),
+                         [("polynomial", 10, 5, "float32", "mixed", 1), ("polynomial", 9, 5, "float32", "fp64", 1),
+                          ("polynomial", 10, 5, "float32", "fp64", 2),
                           ("gto", 12, 4, "float32", "fp64", 2), ("polynomial-laplace", 8, 3, "float64", "mixed", 1),
                           ("gto", 12, 2, "float64", "mixed", 2), ("polynomial", 9, 6, "float64", "mixed", 2)])
 def test_streamed_coefficients_of_several_species(rbf, n, l, dtype, arith, kernel):
     """Bases of many radial functions and species stream their coefficients to
-    the output kernel on short rows, with the explicit choice left alone."""
+    the output kernel on short rows, with the explicit choice left alone; not in the
+    mixed arithmetic, whose scratch is float32."""
     import torch
     from paper_2609_05709_amd.soap import Soap
     wl = _wl((1, 6, 7, 8), rbf, n, l, r_cut=3.5)
