@@ -358,7 +358,13 @@ int plan_launches(soap_ctx *c) {
     // with tiles of two edges or more: three of them per CU in float32, two in
     // float64 (3000-atom water: n_max 8, l_max 6 0.41 against 0.44 ms for k_edge_blocks, float64 0.80
     // against 0.83; at n_max 12, l_max 12, where it runs one workgroup, 2.86
-    // against 1.77)
+    // against 1.77).  Density and edge kernels together over the radial pass and
+    // its kernels, GTO n_max 2..10, l_max 2..8: 1500 atoms and more, float32 with even
+    // n_max and l_max (the compiled sizes) 0.83 to 1.04, the others 0.97 to 1.3; float64
+    // 0.89 to 1.2 but for l_max 7 and 8 at n_max up to 4 (up to 1.48).  Few centers are not
+    // told apart, though k_edge_blocks splits them over workgroups and k_jacobian
+    // doesn't: 480 centers 0.89 to 1.23 (compiled sizes) and 1.0 to 1.6, 198 centers 1.04 to 1.5
+    // and 1.2 to 2.0.
     c->inline_radial = false;
     if (P.rbf == 0 && c->djac_tile >= 0) {
         const int b = plan_jacobian(P);
@@ -863,7 +869,10 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 // The density step of the Jacobian path on the matrix cores: its chunks hold one
 // species, so it takes the structures whose rows have MX_MIN_RUN edges or more
 // per species on average.  (One kernel per neighbour list: a center's results do
-// not depend on the batch that computes it.)
+// not depend on the batch that computes it.)  Whole step over that with k_djs or
+// k_density, by edges per center and species, geometric mean (range): 3.5 1.04 (0.75 to
+// 1.2), 5 1.02 (0.98 to 1.08), 8 1.00 (0.96 to 1.04), 13 0.94 (0.64 to 1.12), 25 0.94 (0.77 to
+// 1.05); bases of n_max 3..12, l_max 4..12.
 bool use_mx(const soap_ctx *c) {
     constexpr double MX_MIN_RUN = 8.0;
     return c->mx_cfg.W > 0 && (double)c->E >= MX_MIN_RUN * (double)c->nc * (double)c->P.S;
